@@ -267,7 +267,7 @@ int64_t carve(const wproj_kernels *k, int64_t nvis, char *base, BinWorkspace &W)
   W.items = (WorkItem *)take((int64_t)sizeof(WorkItem) * max_items);
   const int64_t digit_slots = B.stable ? radix_digit_slots(nvis) : 0;
   W.scan_tmp = (uint32_t *)take(4 * scan_temp_words(std::max({B.n_keys, B.n_tiles, digit_slots})));
-  W.counter = (uint32_t *)take(4);
+  W.queues = (uint32_t *)take(4 * kQueues * kQueueStride);
   W.order = (uint32_t *)take(4 * max_items);
   W.order_cnt = (uint32_t *)take(4 * 2 * kOrderBuckets);
   W.max_items = max_items;
@@ -511,7 +511,7 @@ int wproj_make_kernels(const wproj_params *params, void *stream, wproj_kernels *
   // pair-ordered copy for the fixed-support FP32 gridder
   if (params->precision != WPROJ_F64 && k->uniform_support && k->s_max >= kMinFixedSupport &&
       k->s_max <= kMaxFixedSupport) {
-    k->pair_stride = pair_table_stride(k->s_max);
+    k->pair_stride = pair_stride(k->s_max);
     const int64_t n_sub = (int64_t)n_w * O * O;
     if (hipMalloc(&k->d_tab_pair, (size_t)(n_sub * k->pair_stride) * k->tap_bytes) != hipSuccess)
       return fail(WPROJ_ENOMEM, "device allocation of the pair-ordered table failed");

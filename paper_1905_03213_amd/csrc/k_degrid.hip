@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(64 * kDegridWaves)
                         const Tab *__restrict__ tab, const Rec *__restrict__ rec,
                         const WorkItem *__restrict__ items, const uint32_t *__restrict__ order,
                         const uint32_t *__restrict__ n_items_ptr,
-                        uint32_t *counter, const typename Cd<Real>::T *__restrict__ model,
+                        uint32_t *queues, uint32_t n_queues, const typename Cd<Real>::T *__restrict__ model,
                         typename Cd<Real>::T *__restrict__ out) {
   using C2 = typename Cd<Real>::T;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -100,9 +100,10 @@ __global__ void __launch_bounds__(64 * kDegridWaves)
   const int tiles_per_img = B.ntx * B.nty;
   const bool folding = G.w_mode != WPROJ_W_LINEAR;
 
+  WorkQueue queue(queues, n_queues);
   for (;;) {
     __syncthreads();  // every wave is done with the previous tile and item
-    if (threadIdx.x == 0) s_item = atomicAdd(counter, 1u);
+    if (threadIdx.x == 0) s_item = queue.next();
     __syncthreads();
     const uint32_t it = s_item;
     if (it >= n_items) break;
@@ -276,7 +277,7 @@ __global__ void __launch_bounds__(64 * kTeamWaves)
                            const Tab *__restrict__ tab, uint32_t tab_bytes,
                            const RecordF32 *__restrict__ rec, const WorkItem *__restrict__ items,
                            const uint32_t *__restrict__ order, const uint32_t *__restrict__ n_items_ptr,
-                           uint32_t *counter, const float2 *__restrict__ model, float2 *__restrict__ out) {
+                           uint32_t *queues, uint32_t n_queues, const float2 *__restrict__ model, float2 *__restrict__ out) {
   static_assert(S * S <= 64, "one pass of 64 taps");
   using P = TapPair<Tab>;
   using Raw = typename P::Raw;
@@ -291,7 +292,7 @@ __global__ void __launch_bounds__(64 * kTeamWaves)
   const bool folding = G.w_mode != WPROJ_W_LINEAR;
   const __amdgpu_buffer_rsrc_t tab_rsrc =
       __builtin_amdgcn_make_buffer_rsrc((void *)tab, (short)0, (int)tab_bytes, kBufferWord3);
-  constexpr int kN = S * S, kH = (kN + 1) / 2;
+  constexpr int kN = S * S, kH = pair_half(S, 0);
   constexpr uint32_t kSubBytes = (uint32_t)(2 * kH) * P::kTapBytes;
   const int half = lane >> 5, j = lane & 31;
   uint32_t upper = half ? 0xffffffffu : 0u;
@@ -312,9 +313,10 @@ __global__ void __launch_bounds__(64 * kTeamWaves)
   // lane L ends with record bitrev6(L) of the batch
   const int mine = (int)(__builtin_bitreverse32((uint32_t)lane) >> 26);
 
+  WorkQueue queue(queues, n_queues);
   for (;;) {
     __syncthreads();  // every wave is done with the previous tile and item
-    if (threadIdx.x == 0) s_item = atomicAdd(counter, 1u);
+    if (threadIdx.x == 0) s_item = queue.next();
     __syncthreads();
     const uint32_t it = s_item;
     if (it >= n_items) break;
@@ -448,12 +450,13 @@ hipError_t launch_tap_lane(const wproj_kernels *k, const BinShape &B, const Tile
   e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * wpb, lds);
   if (e != hipSuccess) return e;
   if (per_cu < 1) return hipErrorInvalidConfiguration;
-  if (!k->d_tab_pair || k->pair_stride != pair_table_stride(S)) return hipErrorInvalidValue;
+  if (!k->d_tab_pair || k->pair_stride != pair_stride(S)) return hipErrorInvalidValue;
   const int64_t n_sub = (int64_t)k->params.n_wplanes * k->params.oversample * k->params.oversample;
   hipLaunchKernelGGL(kern, dim3((unsigned)(k->n_cu * per_cu)), dim3(64 * wpb), lds, s, k->geo, B,
                      ts.pitch, ts.rows, (const Tab *)k->d_tab_pair,
                      (uint32_t)(n_sub * k->pair_stride * (int64_t)sizeof(Tab)), (const RecordF32 *)W.rec,
-                     W.items, W.order, W.choff + B.n_tiles, W.counter, (const float2 *)model, (float2 *)out);
+                     W.items, W.order, W.choff + B.n_tiles, W.queues, std::min<uint32_t>(kQueues, (unsigned)(k->n_cu * per_cu)),
+                     (const float2 *)model, (float2 *)out);
   return hipGetLastError();
 }
 
@@ -473,7 +476,8 @@ hipError_t launch_one(const wproj_kernels *k, const BinShape &B, const TileShape
   if (per_cu < 1) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL(kern, dim3((unsigned)(k->n_cu * per_cu)), dim3(64 * wpb), lds, s, k->geo, B,
                      ts.pitch, ts.rows, (const Tab *)k->d_tab, (const Rec *)W.rec,
-                     W.items, W.order, W.choff + B.n_tiles, W.counter, (const C2 *)model, (C2 *)out);
+                     W.items, W.order, W.choff + B.n_tiles, W.queues, std::min<uint32_t>(kQueues, (unsigned)(k->n_cu * per_cu)),
+                     (const C2 *)model, (C2 *)out);
   return hipGetLastError();
 }
 
@@ -512,7 +516,7 @@ hipError_t dispatch_tap_lane(const wproj_kernels *k, const BinShape &B, const Ti
 
 bool tap_lane_degrid(const wproj_kernels *k, const BinShape &B) {
   return k->params.precision == WPROJ_F32 && B.pack_sub && k->s_max <= 8 && k->d_tab_pair != nullptr &&
-         k->pair_stride == pair_table_stride(k->s_max);
+         k->pair_stride == pair_stride(k->s_max);
 }
 
 hipError_t launch_tiled_degrid(const wproj_kernels *k, const BinShape &B, const BinWorkspace &W,
@@ -525,7 +529,7 @@ hipError_t launch_tiled_degrid(const wproj_kernels *k, const BinShape &B, const 
   const int64_t words = nvis * (k->params.precision == WPROJ_F64 ? 4 : 2);
   hipError_t e = launch_fill_u32((uint32_t *)vis_out, words, 0u, s);
   if (e != hipSuccess) return e;
-  if ((e = launch_fill_u32(W.counter, 1, 0u, s)) != hipSuccess) return e;
+  if ((e = launch_fill_u32(W.queues, kQueues * kQueueStride, 0u, s)) != hipSuccess) return e;
   if (tap_lane_degrid(k, B)) return dispatch_tap_lane<float2, kMinFixedSupport>(k, B, ts, W, model_grid, vis_out, s);
   switch (k->params.precision) {
     case WPROJ_F64:

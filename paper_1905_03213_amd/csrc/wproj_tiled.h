@@ -26,6 +26,21 @@ constexpr int kMaxFixedSupport = 16;
 // (15 - c) / 16 of a chunk, down to the smallest).
 constexpr int kOrderBuckets = 16;
 
+// Work items are handed out largest first from kQueues queues, queue q holding items q, q + n,
+// q + 2n, ... of that order: every worker (wavefront or workgroup) takes its next item with
+// an atomic on its queue's head.  Heads lie 128 bytes apart.
+constexpr uint32_t kQueues = 1;
+constexpr uint32_t kQueueStride = 32;
+struct WorkQueue {
+  uint32_t *head;
+  uint32_t q, n_queues;  // n_queues <= workgroups, so that every queue is served
+  __device__ WorkQueue(uint32_t *heads, uint32_t n) : q(blockIdx.x % n), n_queues(n) { head = heads + q * kQueueStride; }
+  // one lane's call: the next item's place in the order (none is left when it is past the end)
+  __device__ uint32_t next() { return atomicAdd(head, 1u) * n_queues + q; }
+};
+// LDS of a compute unit
+constexpr size_t kCuLds = 160 * 1024;
+
 // Partial accumulators per image (weight sums) and per counter, spread by block index.
 constexpr int kSlots = 256;
 
@@ -75,11 +90,18 @@ __host__ __device__ inline uint32_t get_row(const RecordF64 &r) {
 // gfx9 buffer descriptor word 3: 32-bit data format, no swizzle
 constexpr int kBufferWord3 = 0x00020000;
 
-// Paired tap fetch (FP32 arithmetic): one load brings two table entries per lane, lanes
-// 0-31 for the first record of a pair and lanes 32-63 for the second, so a pair of
-// records costs one wide load instead of two narrow ones.  A swap of the upper half of
-// the first entries with the lower half of the second entries (v_permlane32_swap, a
-// VALU operation) then leaves every lane with the same tap of both records.
+// Pair-ordered table (FP32 arithmetic).  The taps of a sub-kernel are cut into passes of 64;
+// entries 2j and 2j + 1 of pass q are taps 64q + j and 64q + pair_half(S, q) + j.  One load
+// brings two entries per lane, lanes 0-31 for the first record of a pair and lanes 32-63 for
+// the second, so a pair of records costs one wide load instead of two narrow ones.  A swap
+// of the upper half of the first entries with the lower half of the second entries
+// (v_permlane32_swap, a VALU operation) then leaves every lane with one tap of both records.
+constexpr int pair_passes(int S) { return (S * S + 63) / 64; }
+constexpr int pair_taps(int S, int q) { return S * S - 64 * q < 64 ? S * S - 64 * q : 64; }
+constexpr int pair_half(int S, int q) { return (pair_taps(S, q) + 1) / 2; }
+// table entries per sub-kernel
+constexpr int pair_stride(int S) { return 64 * (pair_passes(S) - 1) + 2 * pair_half(S, pair_passes(S) - 1); }
+
 template <typename Tab> struct TapPair;
 template <> struct TapPair<float2> {
   typedef uint32_t Raw __attribute__((ext_vector_type(4)));
@@ -129,6 +151,88 @@ __device__ inline double bcast(double v, int j) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
+// A row-replicated register holds the same 16 values in each row of 16 lanes, so a DPP
+// operand with row_newbcast:I reads value I in every lane: the multiply-add or address add
+// that uses a record's field broadcasts it by itself, with no v_readlane before it.
+// After the registers are replicated, dpp_ready covers the two wait states that a DPP read
+// needs after a vector write (the assembler statements below hide the DPP read from the
+// compiler's hazard handling).  DPP reads nothing from a lane that is switched
+// off, so these run with all 64 lanes on.
+template <int I> __device__ inline uint32_t row_bcast(uint32_t v) {
+  static_assert(I >= 0 && I < 16, "a row has 16 lanes");
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + I, 0xF, 0xF, true);
+}
+// s[I] + t, one instruction each (left to itself the compiler shares the broadcast of
+// several sums in a register of its own, one instruction more)
+template <int I> __device__ inline uint32_t add_bcast(uint32_t s, uint32_t t) {
+  uint32_t d;
+  asm("v_add_u32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "=v"(d) : "v"(s), "v"(t), "n"(I));
+  return d;
+}
+// d += s[I] t and d -= s[I] t, fused (one rounding), s row-replicated
+template <int I> __device__ inline void fmac_bcast(float &d, float s, float t) {
+  asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(s), "v"(t), "n"(I));
+}
+template <int I> __device__ inline void fmsc_bcast(float &d, float s, float t) {
+  asm("v_fmac_f32_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(s), "v"(t), "n"(I));
+}
+template <int I> __device__ inline void fmac_bcast(double &d, double s, double t) {
+  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(s), "v"(t), "n"(I));
+}
+template <int I> __device__ inline void fmsc_bcast(double &d, double s, double t) {
+  asm("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(s), "v"(t), "n"(I));
+}
+// v holds 32 values in each half wavefront (value i in lanes i and 32 + i): out[0] is
+// values 0..15 and out[1] values 16..31, row-replicated.
+__device__ inline void replicate16(uint32_t v, uint32_t (&out)[2]) {
+  const auto h = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  out[0] = h[0];
+  out[1] = h[1];
+}
+__device__ inline void replicate16(float v, float (&out)[2]) {
+  uint32_t r[2];
+  replicate16(__float_as_uint(v), r);
+  out[0] = __uint_as_float(r[0]);
+  out[1] = __uint_as_float(r[1]);
+}
+__device__ inline void replicate16(double v, double (&out)[2]) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  uint32_t lo[2], hi[2];
+  replicate16((uint32_t)b, lo);
+  replicate16((uint32_t)(b >> 32), hi);
+  for (int g = 0; g < 2; ++g)
+    out[g] = __longlong_as_double((long long)(((unsigned long long)hi[g] << 32) | lo[g]));
+}
+
+template <typename A, typename B, typename C, typename D>
+__device__ inline void dpp_ready(A &a, B &b, C &c, D &d) {
+  asm volatile("s_nop 1" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+}
+
+// f(std::integral_constant<int, 0>{}) ... f(std::integral_constant<int, N - 1>{}).
+template <int I, int N, typename F> __device__ inline void static_for(F &&f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
+// Complex cells at LDS byte addresses.
+template <typename T> using LdsPtr = __attribute__((address_space(3))) T *;
+typedef float Vec2f __attribute__((ext_vector_type(2)));
+typedef double Vec2d __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t lds_address(void *p) { return (uint32_t)(uintptr_t)(LdsPtr<unsigned char>)(unsigned char *)p; }
+__device__ inline void lds_read(uint32_t addr, float2 &v) {
+  const Vec2f t = *(LdsPtr<Vec2f>)(uintptr_t)addr;
+  v = make_float2(t.x, t.y);
+}
+__device__ inline void lds_read(uint32_t addr, double2 &v) {
+  const Vec2d t = *(LdsPtr<Vec2d>)(uintptr_t)addr;
+  v = make_double2(t.x, t.y);
+}
+__device__ inline void lds_write(uint32_t addr, const float2 &v) { *(LdsPtr<Vec2f>)(uintptr_t)addr = Vec2f{v.x, v.y}; }
+__device__ inline void lds_write(uint32_t addr, const double2 &v) { *(LdsPtr<Vec2d>)(uintptr_t)addr = Vec2d{v.x, v.y}; }
+
 // Binning geometry: tiles of `tile` cells, ntx x nty per image, kw keys per tile
 // (n_wplanes when the plane is part of the key, else 1).
 struct BinShape {
@@ -161,7 +265,7 @@ struct BinWorkspace {
   uint32_t *choff;     // [n_tiles + 1]; choff[n_tiles] = number of work items
   WorkItem *items;     // [max_items]
   uint32_t *scan_tmp;  // scan_temp_words(max(n_keys, n_tiles))
-  uint32_t *counter;   // [1] work-queue head
+  uint32_t *queues;    // [kQueues * kQueueStride] heads of the work queues
   uint32_t *order;     // [max_items] work-item indices, largest items first
   uint32_t *order_cnt; // [2 * kOrderBuckets] per size class: item count, placement cursor
   int64_t max_items;   // capacity of items, order and partial
@@ -204,14 +308,16 @@ TileShape tile_shape(const wproj_kernels *k, int tile);
 // Row pitch (complex cells) of the degridder's tile copy when records are binned for
 // degridding only: the smallest odd pitch >= T + S_max - 1.
 int degrid_pitch(const wproj_kernels *k, int tile);
-// Entries per sub-kernel of the pair-ordered table for support S, and the launch that
-// fills k->d_tab_pair from k->d_tab.
-int64_t pair_table_stride(int S);
+// Fills k->d_tab_pair from k->d_tab.
 hipError_t launch_pair_table(const wproj_kernels *k, hipStream_t s);
 // The tile gridder into the work items' partial tiles, then their sum into the grid.
 // With vis != nullptr the records are row-carrying (a plan) and W V is formed from vis.
 hipError_t launch_tiled_grid(const wproj_kernels *k, const BinShape &B, const BinWorkspace &W,
                              void *grid, hipStream_t s, const void *vis = nullptr);
+hipError_t launch_tiled_grid_f16(const wproj_kernels *k, const BinShape &B, const TileShape &ts, const BinWorkspace &W,
+                                 void *grid, const void *vis, hipStream_t s);
+hipError_t launch_tiled_grid_f64(const wproj_kernels *k, const BinShape &B, const TileShape &ts, const BinWorkspace &W,
+                                 void *grid, const void *vis, hipStream_t s);
 hipError_t launch_tile_reduce(const wproj_kernels *k, const BinShape &B, const BinWorkspace &W,
                               void *grid, hipStream_t s);
 // Whether launch_tiled_degrid takes the one-tap-per-lane degridder (FP32 arithmetic and
