@@ -28,8 +28,12 @@ constexpr int kOrderBuckets = 16;
 
 // Work items are handed out largest first from kQueues queues, queue q holding items q, q + n,
 // q + 2n, ... of that order: every worker (wavefront or workgroup) takes its next item with
-// an atomic on its queue's head.  Heads lie 128 bytes apart.
-constexpr uint32_t kQueues = 1;
+// an atomic on its queue's head.  One head for all hands out only an item every 9 ns: 2.4 ms
+// for the 2.6e5 tiles of 64 images of 1024^2 (16-cell tiles; 1.1 ms with 8, 16 or 32 heads,
+// 1.14 with 128), and 0.42 ms instead of 0.28 for 1e7 rows on 16 layers of 2048^2.  Queues
+// of their own for the small items, or a first item by the worker's number, measured slower
+// (1.46 against 1.38 ms on 5.6e7 records).  Heads lie 128 bytes apart.
+constexpr uint32_t kQueues = 16;
 constexpr uint32_t kQueueStride = 32;
 struct WorkQueue {
   uint32_t *head;
