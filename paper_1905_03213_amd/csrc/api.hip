@@ -217,7 +217,23 @@ hipEvent_t take_event(wproj_kernels *k) {
 constexpr int64_t kAlign = 256;
 inline int64_t align_up(int64_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-BinShape bin_shape(const wproj_kernels *k) {
+// Binning of a single call (bin_shape once): the bins are whole tiles, since the w-plane in
+// the key only adds bins (2048^2, 6.5e7 rows, 32-cell tiles: binning 1.28 -> 1.06 ms, while
+// the gridder, whose taps come from L2 either way, takes 1.39 instead of 1.37).  Fewer bins
+// are busier, so a bin has several counters, a block of the key pass using one of them
+// (2^16 counters in all measured best: 1.06 ms against 1.09 with half and 1.11 with twice as
+// many; one counter a bin 1.91), but at least 4 while 2^18 hold them (1e7 rows on 16 layers
+// of 2048^2, 65536 bins: 0.72 ms with 1, 0.51 with 4, 0.49 with 8; 64 images of 1024^2 with
+// the aggregated key pass: 1.10, 1.13, 1.37), and never more counters than the planes' bins
+// would have needed, so the workspace does not grow.
+constexpr int kMaxLog2Rep = 4;
+constexpr int64_t kBestCounters = 1ll << 16, kMostCounters = 1ll << 18;
+// Counters are spread over cache lines where there are few of them: with the planes' bins,
+// 1.7e5 counters (1024^2, 23 planes) 0.52 -> 0.46 ms, but 5.2e5 (2048^2, 128 planes)
+// 1.28 -> 1.37 ms.
+constexpr int64_t kMaxSpread = 1ll << 18;
+
+BinShape bin_shape(const wproj_kernels *k, bool once = false) {
   BinShape B;
   B.tile = k->tile;
   B.log2_tile = 0;
@@ -236,6 +252,19 @@ BinShape bin_shape(const wproj_kernels *k) {
                n_sub <= (1ll << (32 - kLdsBits));
   B.n_tiles = (int64_t)k->geo.n_grids * B.ntx * B.nty;
   B.n_keys = B.n_tiles * B.kw;
+  B.log2_rep = 0;
+  if (once && B.pack_sub && !B.stable) {
+    const int64_t room = B.n_keys;
+    B.kw = 1;
+    B.n_keys = B.n_tiles;
+    auto fits = [&](int r) {
+      const int64_t c = B.n_keys << r;
+      return c <= room && (c <= kBestCounters || (r <= 2 && c <= kMostCounters));
+    };
+    while (B.log2_rep < kMaxLog2Rep && fits(B.log2_rep + 1)) ++B.log2_rep;
+  }
+  B.n_counts = B.n_keys << B.log2_rep;
+  B.spread = B.n_counts <= kMaxSpread;
   return B;
 }
 
@@ -260,13 +289,13 @@ int64_t carve(const wproj_kernels *k, int64_t nvis, char *base, BinWorkspace &W)
   // the record's tap word
   W.slots = (uint32_t *)take(4 * nvis * (B.pack_sub ? 3 : 4));
   W.rec = take(rec_bytes * nvis);
-  W.count = (uint32_t *)take(4 * B.n_keys);
-  W.offset = (uint32_t *)take(4 * (B.n_keys + 1));
+  W.count = (uint32_t *)take(4 * ((B.n_counts + 255) & ~255ll));
+  W.offset = (uint32_t *)take(4 * (B.n_counts + 1));
   W.nch = (uint32_t *)take(4 * B.n_tiles);
   W.choff = (uint32_t *)take(4 * (B.n_tiles + 1));
   W.items = (WorkItem *)take((int64_t)sizeof(WorkItem) * max_items);
   const int64_t digit_slots = B.stable ? radix_digit_slots(nvis) : 0;
-  W.scan_tmp = (uint32_t *)take(4 * scan_temp_words(std::max({B.n_keys, B.n_tiles, digit_slots})));
+  W.scan_tmp = (uint32_t *)take(4 * scan_temp_words(std::max({B.n_counts, B.n_tiles, digit_slots})));
   W.queues = (uint32_t *)take(4 * kQueues * kQueueStride);
   W.order = (uint32_t *)take(4 * max_items);
   W.order_cnt = (uint32_t *)take(4 * 2 * kOrderBuckets);
@@ -634,7 +663,7 @@ int wproj_grid(const wproj_kernels *k, int64_t nvis, const double *uvw, const vo
   if (k->n_taps > (int64_t)kTapMask)
     return fail(WPROJ_EUNSUPPORTED, "kernel tables of %lld taps exceed the tiled gridder's 2^26",
                 (long long)k->n_taps);
-  const BinShape B = bin_shape(k);
+  const BinShape B = bin_shape(k, true);
   if (B.n_keys >= max_keys(k))
     return fail(WPROJ_EUNSUPPORTED, "%lld bins (images x tiles) exceed the tiled gridder's 31-bit keys",
                 (long long)B.n_keys);
@@ -784,7 +813,7 @@ int wproj_degrid(const wproj_kernels *k, int64_t nvis, const double *uvw, const 
   if (k->n_taps > (int64_t)kTapMask)
     return fail(WPROJ_EUNSUPPORTED, "kernel tables of %lld taps exceed the tiled degridder's 2^26",
                 (long long)k->n_taps);
-  BinShape B = bin_shape(k);
+  BinShape B = bin_shape(k, true);
   if (B.n_keys >= max_keys(k))
     return fail(WPROJ_EUNSUPPORTED, "%lld bins (images x tiles) exceed the tiled degridder's 31-bit keys",
                 (long long)B.n_keys);

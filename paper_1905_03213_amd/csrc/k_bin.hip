@@ -5,11 +5,12 @@
 // key's first position (Eq. 6), then a reorder.  The same counting-sort pattern is
 // used here, re-keyed so that each group is a uv-tile of the grid (and, within it,
 // one w-plane) that a workgroup can accumulate in LDS:
-//   key pass     classify each visibility, key = ((img * nty + ty) * ntx + tx) * kw + p,
-//                count[key] += 1 returning the visibility's slot within its key;
+//   key pass     classify each visibility, key = ((img * nty + ty) * ntx + tx) * kw + p
+//                (kw = 1 and no p where a single call bins by tile alone), add 1 to one of
+//                the key's counters, which returns the visibility's slot in that counter;
 //                also sumW per image and the drop/clamp/bad-weight counters;
-//   scan         exclusive prefix sum of count (Eq. 6);
-//   scatter      record of visibility j goes to offset[key] + slot;
+//   scan         exclusive prefix sum of the counters (Eq. 6);
+//   scatter      record of visibility j goes to offset[counter] + slot;
 //   work list    each tile's record range split into chunks of at most `chunk` records.
 // Count atomics are aggregated over runs of a wavefront's lanes that share a key, so a
 // record's place inside its bin follows the order in which the runs' atomics land (the
@@ -42,6 +43,8 @@ constexpr uint32_t kFoldBit = 0x80000000u;
 // pass, +0.01 ms on cfg3's per-plane supports).
 constexpr int kBinBlock = 256;
 constexpr int kKeyVpt = 2;
+constexpr int kLog2KeySpan = 9;  // rows of a block of the key pass
+static_assert(kBinBlock * kKeyVpt == 1 << kLog2KeySpan, "rows per block");
 
 // Runs of consecutive lanes with equal keys (rows of one baseline's channels are adjacent
 // and share tiles and planes, so a wavefront holds a few long runs).  The first lane of
@@ -77,6 +80,24 @@ __device__ inline uint32_t bin_key(const Geometry &G, const BinShape &B, int img
   const uint32_t g = (uint32_t)grid_of(G, img, f);
   const uint32_t tile = (g * (uint32_t)B.nty + ty) * (uint32_t)B.ntx + tx;
   return B.kw > 1 ? tile * (uint32_t)B.kw + (uint32_t)f.p : tile;
+}
+
+// Counter of a key for a block of the key pass: the blocks spread over the key's counters.
+__device__ inline uint32_t counter_of(const BinShape &B, uint32_t key, uint32_t block) {
+  return (key << B.log2_rep) | (block & ((1u << B.log2_rep) - 1u));
+}
+
+// Where counter c of n lies when the counters are spread: column c mod 256 of rows of 256,
+// stored column by column.  Atomics on one cache line take turns (about 10 ns each), and
+// neighbouring tiles and a key's own counters are busy at the same time, so they are kept on
+// different lines: with 8 counters per key side by side the key pass gained nothing from
+// them (1024^2 image, 4e6 rows: binning 0.67 ms, spread 0.24).
+__device__ inline int64_t counter_place(uint32_t c, int64_t n) {
+  return (int64_t)(c & 255u) * ((n + 255) >> 8) + (c >> 8);
+}
+__device__ inline uint32_t *counter_at(const BinShape &B, uint32_t *count, uint32_t key, uint32_t block) {
+  const uint32_t c = counter_of(B, key, block);
+  return count + (B.spread ? counter_place(c, B.n_counts) : (int64_t)c);
 }
 
 __device__ inline double wave_sum(double v) {
@@ -195,7 +216,7 @@ __global__ void __launch_bounds__(kBinBlock)
   for (int i = 0; i < V; ++i) {
     run[i] = run_of(key[i]);
     uint32_t g = 0;
-    if (run[i].lead) g = atomicAdd(&count[key[i]], run[i].len);
+    if (run[i].lead) g = atomicAdd(counter_at(B, count, key[i], blockIdx.x), run[i].len);
     got[i] = g;
   }
 #pragma unroll
@@ -260,6 +281,8 @@ __global__ void __launch_bounds__(kBinBlock)
 constexpr int kAggThreads = 512;
 constexpr int kAggVpt = 4;
 constexpr int kAggSpan = kAggThreads * kAggVpt;
+constexpr int kLog2AggSpan = 11;
+static_assert(kAggSpan == 1 << kLog2AggSpan, "rows per block");
 constexpr int kAggSlots = 2048;  // a power of two
 constexpr int kAggProbes = 16;
 constexpr uint32_t kDirect = 0xffffffffu;  // entry index of a run counted globally
@@ -356,7 +379,7 @@ __global__ void __launch_bounds__(kAggThreads)
         }
         h = (h + 1u) & (uint32_t)(kAggSlots - 1);
       }
-      r = e == kDirect ? atomicAdd(&count[key[i]], run[i].len) : atomicAdd(&h_cnt[e], run[i].len);
+      r = e == kDirect ? atomicAdd(counter_at(B, count, key[i], blockIdx.x), run[i].len) : atomicAdd(&h_cnt[e], run[i].len);
     }
     where[i] = e;
     rank[i] = r;
@@ -369,7 +392,7 @@ __global__ void __launch_bounds__(kAggThreads)
     const int e = threadIdx.x + q * kAggThreads;
     const uint32_t k = h_key[e];
     uint32_t b = 0;
-    if (k != kInvalid) b = atomicAdd(&count[k], h_cnt[e]);
+    if (k != kInvalid) b = atomicAdd(counter_at(B, count, k, blockIdx.x), h_cnt[e]);
     gb[q] = b;
   }
 #pragma unroll
@@ -455,12 +478,12 @@ __device__ inline bool make_record(int64_t nvis, const Cplx *__restrict__ vis, c
 
 // Record of visibility j to offset[key] + its slot; V visibilities per thread
 // (j = block kBinBlock V + i kBinBlock + thread), every record built before the first is
-// stored.
+// stored.  2^log2_span rows belong to one block of the key pass.
 template <typename Real, typename Cplx, typename Rec, bool TAPWORD, int V>
 __global__ void __launch_bounds__(kBinBlock)
-    scatter_kernel(int64_t nvis, const Cplx *__restrict__ vis, const Real *__restrict__ wt,
-                   const uint32_t *__restrict__ slots, const uint32_t *__restrict__ offset, int S_fix,
-                   Rec *__restrict__ rec) {
+    scatter_kernel(BinShape B, int log2_span, int64_t nvis, const Cplx *__restrict__ vis,
+                   const Real *__restrict__ wt, const uint32_t *__restrict__ slots,
+                   const uint32_t *__restrict__ offset, int S_fix, Rec *__restrict__ rec) {
   Rec r[V];
   uint32_t key[V];
   bool ok[V];
@@ -473,7 +496,7 @@ __global__ void __launch_bounds__(kBinBlock)
   }
 #pragma unroll
   for (int i = 0; i < V; ++i)
-    if (ok[i]) rec[offset[key[i]] + slots[j[i]]] = r[i];
+    if (ok[i]) rec[offset[counter_of(B, key[i], (uint32_t)(j[i] >> log2_span))] + slots[j[i]]] = r[i];
 }
 
 // ---- stable binning: least-significant-digit radix sort of the bin keys ----
@@ -640,54 +663,65 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// ---- exclusive scan of uint32 counts (three phases) ----
-constexpr int kScanBlock = 1024;
-constexpr int kScanItems = 4;
+// ---- exclusive scan of uint32 counts ----
+//
+// Tiles of kScanTile values: tile sums, then every tile adds the sums before it to its own
+// scan (two launches; beyond kScanSelf tiles the sums are scanned by a block of their own
+// first).  A tile is 16 rows of 256 values, thread t holding column t, which suits both
+// layouts of the input: plain, and spread (counter_place).
+constexpr int kScanBlock = 256;
+constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanBlock * kScanItems;
+constexpr int64_t kScanSelf = 2048;
 
+// Sum over the block's lanes before this one; total receives the block's sum.
 __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t *sh, uint32_t &total) {
-  // Hillis-Steele over the block in LDS (1024 entries)
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-  for (int off = 1; off < kScanBlock; off <<= 1) {
-    uint32_t add = t >= off ? sh[t - off] : 0u;
-    __syncthreads();
-    sh[t] += add;
-    __syncthreads();
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  uint32_t incl = v;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t up = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += up;
   }
-  total = sh[kScanBlock - 1];
-  uint32_t incl = sh[t];
+  if (lane == 63) sh[wid] = incl;
   __syncthreads();
-  return incl - v;
+  uint32_t before = 0;
+  total = 0;
+  for (int k = 0; k < (int)(blockDim.x >> 6); ++k) {
+    const uint32_t s = sh[k];
+    if (k < wid) before += s;
+    total += s;
+  }
+  __syncthreads();
+  return before + incl - v;
 }
 
+template <bool SPREAD>
+__device__ inline void scan_load(const uint32_t *__restrict__ in, int64_t n, uint32_t (&v)[kScanItems]) {
+  const int64_t base = (int64_t)blockIdx.x * kScanTile;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    const int64_t i = base + k * kScanBlock + threadIdx.x;
+    v[k] = i < n ? in[SPREAD ? counter_place((uint32_t)i, n) : i] : 0u;
+  }
+}
+
+template <bool SPREAD>
 __global__ void __launch_bounds__(kScanBlock)
-    scan_tiles_kernel(const uint32_t *__restrict__ in, uint32_t *__restrict__ out, int64_t n,
-                      uint32_t *__restrict__ tile_sums) {
-  __shared__ uint32_t sh[kScanBlock];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  uint32_t v[kScanItems];
-  uint32_t s = 0;
-  for (int i = 0; i < kScanItems; ++i) {
-    v[i] = base + i < n ? in[base + i] : 0u;
-    s += v[i];
-  }
-  uint32_t total;
-  uint32_t ex = block_exclusive_scan(s, sh, total);
-  for (int i = 0; i < kScanItems; ++i) {
-    if (base + i < n) out[base + i] = ex;
-    ex += v[i];
-  }
+    scan_sums_of_tiles_kernel(const uint32_t *__restrict__ in, int64_t n, uint32_t *__restrict__ tile_sums) {
+  __shared__ uint32_t sh[kScanBlock / 64];
+  uint32_t v[kScanItems], s = 0, total;
+  scan_load<SPREAD>(in, n, v);
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) s += v[k];
+  block_exclusive_scan(s, sh, total);
   if (threadIdx.x == 0) tile_sums[blockIdx.x] = total;
 }
 
-// Scans the per-tile sums in place (one block, any count) and writes the grand total.
-__global__ void __launch_bounds__(kScanBlock)
-    scan_sums_kernel(uint32_t *sums, int64_t n_tiles, uint32_t *total_out) {
-  __shared__ uint32_t sh[kScanBlock];
+// Scans the tile sums in place (one block, any count).
+__global__ void __launch_bounds__(1024) scan_sums_kernel(uint32_t *sums, int64_t n_tiles) {
+  __shared__ uint32_t sh[1024 / 64];
   uint32_t carry = 0;
-  for (int64_t b = 0; b < n_tiles; b += kScanBlock) {
+  for (int64_t b = 0; b < n_tiles; b += 1024) {
     const int64_t i = b + threadIdx.x;
     const uint32_t v = i < n_tiles ? sums[i] : 0u;
     uint32_t total;
@@ -695,13 +729,51 @@ __global__ void __launch_bounds__(kScanBlock)
     if (i < n_tiles) sums[i] = carry + ex;
     carry += total;
   }
-  if (threadIdx.x == 0) *total_out = carry;
 }
 
-__global__ void __launch_bounds__(256)
-    scan_add_kernel(uint32_t *out, int64_t n, const uint32_t *__restrict__ tile_prefix) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] += tile_prefix[i / kScanTile];
+// out[i] = sum of the values before i, out[n] = the grand total.  SELF: tile_sums holds sums
+// (the block adds up those before its own), else their scan.
+template <bool SPREAD, bool SELF>
+__global__ void __launch_bounds__(kScanBlock)
+    scan_tiles_kernel(const uint32_t *__restrict__ in, uint32_t *__restrict__ out, int64_t n,
+                      const uint32_t *__restrict__ tile_sums) {
+  __shared__ uint32_t sh[kScanBlock / 64];
+  __shared__ uint32_t tile[kScanTile + kScanTile / kScanItems];
+  auto at = [](int i) { return i + i / kScanItems; };  // padded against bank conflicts
+  const int t = threadIdx.x;
+  uint32_t v[kScanItems], total;
+  scan_load<SPREAD>(in, n, v);
+  uint32_t before;
+  if constexpr (SELF) {
+    uint32_t mine = 0;
+    for (int64_t b = t; b < (int64_t)blockIdx.x; b += kScanBlock) mine += tile_sums[b];
+    block_exclusive_scan(mine, sh, before);
+  } else {
+    before = tile_sums[blockIdx.x];
+  }
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) tile[at(k * kScanBlock + t)] = v[k];
+  __syncthreads();
+  uint32_t s = 0;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    v[k] = tile[at(t * kScanItems + k)];
+    s += v[k];
+  }
+  uint32_t run = before + block_exclusive_scan(s, sh, total);
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    tile[at(t * kScanItems + k)] = run;
+    run += v[k];
+  }
+  __syncthreads();
+  const int64_t base = (int64_t)blockIdx.x * kScanTile;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    const int64_t i = base + k * kScanBlock + t;
+    if (i < n) out[i] = tile[at(k * kScanBlock + t)];
+  }
+  if (blockIdx.x == gridDim.x - 1 && t == 0) out[n] = before + total;
 }
 
 __global__ void __launch_bounds__(256)
@@ -803,12 +875,13 @@ hipError_t place_records(const wproj_kernels *k, const BinShape &B, int64_t nvis
                          const BinWorkspace &W, int S_fix, hipStream_t s) {
   const dim3 grid(nblk(nvis, kBinBlock)), block(kBinBlock);
   if (!B.stable) {
+    const int log2_span = B.aggregate ? kLog2AggSpan : kLog2KeySpan;
     if (!TAPWORD && !B.aggregate)
       hipLaunchKernelGGL((scatter_kernel<Real, Cplx, Rec, TAPWORD, 2>), dim3(nblk(nvis, 2 * kBinBlock)), block, 0, s,
-                         nvis, (const Cplx *)vis, (const Real *)wt, W.slots, W.offset, S_fix, (Rec *)W.rec);
+                         B, log2_span, nvis, (const Cplx *)vis, (const Real *)wt, W.slots, W.offset, S_fix, (Rec *)W.rec);
     else
-      hipLaunchKernelGGL((scatter_kernel<Real, Cplx, Rec, TAPWORD, 1>), grid, block, 0, s, nvis, (const Cplx *)vis,
-                         (const Real *)wt, W.slots, W.offset, S_fix, (Rec *)W.rec);
+      hipLaunchKernelGGL((scatter_kernel<Real, Cplx, Rec, TAPWORD, 1>), grid, block, 0, s, B, log2_span, nvis,
+                         (const Cplx *)vis, (const Real *)wt, W.slots, W.offset, S_fix, (Rec *)W.rec);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(sort_key_kernel, grid, block, 0, s, nvis, (uint32_t)B.n_keys, W.slots, W.sort_keys[0]);
@@ -835,7 +908,7 @@ hipError_t place_records(const wproj_kernels *k, const BinShape &B, int64_t nvis
     cur ^= 1;
   }
   hipLaunchKernelGGL((gather_kernel<Real, Cplx, Rec, TAPWORD>), grid, block, 0, s, nvis, (const Cplx *)vis,
-                     (const Real *)wt, W.slots, vals, W.offset + B.n_keys, S_fix, (Rec *)W.rec);
+                     (const Real *)wt, W.slots, vals, W.offset + B.n_counts, S_fix, (Rec *)W.rec);
   return hipGetLastError();
 }
 
@@ -853,21 +926,29 @@ int64_t radix_digit_slots(int64_t nvis) {
   return std::max<int64_t>(1, (nvis + kRadixTile - 1) / kRadixTile) * kRadixDigits;
 }
 
-// out[i] = sum_{k < i} in[i], out[n] = total (out has n + 1 entries).
-hipError_t launch_exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp,
-                                 hipStream_t s) {
+template <bool SPREAD>
+static hipError_t exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {
   const int64_t tiles = (n + kScanTile - 1) / kScanTile;
-  hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)tiles), dim3(kScanBlock), 0, s, in, out, n,
-                     tmp);
-  hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(kScanBlock), 0, s, tmp, tiles, out + n);
-  hipLaunchKernelGGL(scan_add_kernel, dim3(nblk(n, 256)), dim3(256), 0, s, out, n, tmp);
+  const dim3 grid((unsigned)tiles), block(kScanBlock);
+  if (tiles > 1) hipLaunchKernelGGL(scan_sums_of_tiles_kernel<SPREAD>, grid, block, 0, s, in, n, tmp);
+  if (tiles <= kScanSelf) {
+    hipLaunchKernelGGL((scan_tiles_kernel<SPREAD, true>), grid, block, 0, s, in, out, n, tmp);
+  } else {
+    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(1024), 0, s, tmp, tiles);
+    hipLaunchKernelGGL((scan_tiles_kernel<SPREAD, false>), grid, block, 0, s, in, out, n, tmp);
+  }
   return hipGetLastError();
+}
+
+// out[i] = sum_{k < i} in[i], out[n] = total (out has n + 1 entries).
+hipError_t launch_exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {
+  return exclusive_scan<false>(in, out, n, tmp, s);
 }
 
 hipError_t launch_plan_rows(const wproj_kernels *k, const BinShape &B, const BinWorkspace &W, int64_t nvis,
                             uint32_t *rows, hipStream_t s) {
   // plans hold row-carrying records: RecordF64 in FP64, RecordF32 otherwise
-  const uint32_t *total = W.offset + B.n_keys;
+  const uint32_t *total = W.offset + B.n_counts;
   if (k->params.precision == WPROJ_F64)
     hipLaunchKernelGGL(plan_rows_kernel<RecordF64>, dim3(nblk(nvis, 256)), dim3(256), 0, s,
                        (const RecordF64 *)W.rec, total, nvis, rows);
@@ -881,7 +962,7 @@ hipError_t launch_bin(const wproj_kernels *k, const BinShape &B, int64_t nvis, c
                       const void *vis, const void *wt, const int64_t *img_off, double *wsum,
                       int64_t *counters, const BinWorkspace &W, hipStream_t s) {
   const Geometry &G = k->geo;
-  hipError_t e = launch_fill_u32(W.count, B.n_keys, 0u, s);
+  hipError_t e = launch_fill_u32(W.count, (B.n_counts + 255) & ~255ll, 0u, s);
   if (e != hipSuccess) return e;
   // zero the slot accumulators (bit pattern 0 is 0.0 and 0)
   if ((e = launch_fill_u32((uint32_t *)W.wslots, 2 * kSlots * (int64_t)k->params.n_images, 0u, s)) != hipSuccess)
@@ -924,7 +1005,9 @@ hipError_t launch_bin(const wproj_kernels *k, const BinShape &B, int64_t nvis, c
                        s, ni, W.wslots, W.cslots, wsum, reinterpret_cast<unsigned long long *>(counters));
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if ((e = launch_exclusive_scan(W.count, W.offset, B.n_keys, W.scan_tmp, s)) != hipSuccess) return e;
+  e = B.spread ? exclusive_scan<true>(W.count, W.offset, B.n_counts, W.scan_tmp, s)
+               : exclusive_scan<false>(W.count, W.offset, B.n_counts, W.scan_tmp, s);
+  if (e != hipSuccess) return e;
   if (k->params.precision == WPROJ_F64)
     e = tapword ? place_records<double, double2, RecordF64, true>(k, B, nvis, vis, wt, W, S_fix, s)
                 : place_records<double, double2, RecordF64, false>(k, B, nvis, vis, wt, W, S_fix, s);
@@ -936,11 +1019,11 @@ hipError_t launch_bin(const wproj_kernels *k, const BinShape &B, int64_t nvis, c
   if (e != hipSuccess) return e;
   // work list: per tile, ceil(records / chunk) items
   hipLaunchKernelGGL(chunk_count_kernel, dim3(nblk(B.n_tiles, 256)), dim3(256), 0, s, W.offset,
-                     B.n_tiles, B.kw, B.chunk, W.nch);
+                     B.n_tiles, B.kw << B.log2_rep, B.chunk, W.nch);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_exclusive_scan(W.nch, W.choff, B.n_tiles, W.scan_tmp, s)) != hipSuccess) return e;
   hipLaunchKernelGGL(chunk_emit_kernel, dim3(nblk(B.n_tiles, 256)), dim3(256), 0, s, W.offset,
-                     B.n_tiles, B.kw, B.chunk, W.choff, W.items);
+                     B.n_tiles, B.kw << B.log2_rep, B.chunk, W.choff, W.items);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // largest-first order of the work items (their number is choff[n_tiles] <= max_items)
   if ((e = launch_fill_u32(W.order_cnt, 2 * kOrderBuckets, 0u, s)) != hipSuccess) return e;

@@ -238,7 +238,7 @@ __device__ inline void lds_write(uint32_t addr, const float2 &v) { *(LdsPtr<Vec2
 __device__ inline void lds_write(uint32_t addr, const double2 &v) { *(LdsPtr<Vec2d>)(uintptr_t)addr = Vec2d{v.x, v.y}; }
 
 // Binning geometry: tiles of `tile` cells, ntx x nty per image, kw keys per tile
-// (n_wplanes when the plane is part of the key, else 1).
+// (n_wplanes when the plane is part of the key, else 1), 2^log2_rep counters per key.
 struct BinShape {
   int tile;
   int log2_tile;     // tile = 1 << log2_tile
@@ -250,7 +250,10 @@ struct BinShape {
   int aggregate;     // the key pass aggregates counts per block in LDS (wproj_params::bin_aggregate)
   int stable;        // records keep input order inside a bin (wproj_params::stable_bins)
   int64_t n_tiles;   // n_images * ntx * nty
+  int log2_rep;      // a key's visibilities are counted in 2^log2_rep counters, by the key pass's block
+  int spread;        // neighbouring counters are stored on different cache lines (counter_place)
   int64_t n_keys;    // n_tiles * kw
+  int64_t n_counts;  // n_keys << log2_rep
 };
 
 struct WorkItem {
@@ -263,8 +266,8 @@ struct WorkItem {
 struct BinWorkspace {
   uint32_t *slots;     // [3 nvis] (slot, key, record word) when pack_sub, else [4 nvis] (and tap word)
   void *rec;           // [nvis] RecordF32 / RecordF32P / RecordF64
-  uint32_t *count;     // [n_keys]
-  uint32_t *offset;    // [n_keys + 1]
+  uint32_t *count;     // [n_counts rounded up to 256]
+  uint32_t *offset;    // [n_counts + 1]: a key's records start at offset[key << log2_rep]
   uint32_t *nch;       // [n_tiles]
   uint32_t *choff;     // [n_tiles + 1]; choff[n_tiles] = number of work items
   WorkItem *items;     // [max_items]
