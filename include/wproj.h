@@ -100,8 +100,9 @@ typedef struct {
   int32_t n_images;         /* >= 1: independent images gridded in one call (e.g. channels) */
   int32_t algorithm;        /* wproj_algorithm */
   int32_t tile;             /* tiled gridder tile side: 0 = default (16), else 16, 32 or 64 */
-  int32_t chunk;            /* tiled gridder work-item length in records: 0 = default (2048),
-                               else 256..65536 */
+  int32_t chunk;            /* tiled gridder work-item length in records: 0 = default (2048,
+                               less in calls of few rows
+                               without stable_bins), else 256..65536 */
   int32_t w_mode;           /* wproj_w_mode (0 = linear planes over [-w_max, w_max]).  The fold
                                halves the planes (and tables) needed for a given plane spacing:
                                with a real sky V(-u,-v,-w) = conj(V(u,v,w)), so Re of the image

@@ -217,23 +217,27 @@ hipEvent_t take_event(wproj_kernels *k) {
 constexpr int64_t kAlign = 256;
 inline int64_t align_up(int64_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-// Binning of a single call (bin_shape once): the bins are whole tiles, since the w-plane in
-// the key only adds bins (2048^2, 6.5e7 rows, 32-cell tiles: binning 1.28 -> 1.06 ms, while
-// the gridder, whose taps come from L2 either way, takes 1.39 instead of 1.37).  Fewer bins
-// are busier, so a bin has several counters, a block of the key pass using one of them
-// (2^16 counters in all measured best: 1.06 ms against 1.09 with half and 1.11 with twice as
-// many; one counter a bin 1.91), but at least 4 while 2^18 hold them (1e7 rows on 16 layers
-// of 2048^2, 65536 bins: 0.72 ms with 1, 0.51 with 4, 0.49 with 8; 64 images of 1024^2 with
-// the aggregated key pass: 1.10, 1.13, 1.37), and never more counters than the planes' bins
-// would have needed, so the workspace does not grow.
+// Binning of a single call (bin_shape with its rows): the bins are whole tiles, since the
+// w-plane in the key only adds bins (2048^2, 6.5e7 rows, 32-cell tiles: binning 1.28 -> 1.06
+// ms, while the gridder, whose taps come from L2 either way, takes 1.39 instead of 1.37).
+// Fewer bins are busier, so a bin has several counters, a block of the key pass using one of
+// them.  2^16 counters in all measured best for 4e6 rows on 1024^2 (0.22 ms, 0.24 with half
+// as many), 2^15 for the 6.5e7 rows (1.06 ms, 1.11 with 2^16, 1.09 with 2^14, 1.91 with one a
+// bin), whose scattered record writes gain from fewer open ends.  A bin gets at least 4
+// while 2^18 hold them (1e7 rows on 16 layers of 2048^2, 65536 bins: 0.72 ms with 1, 0.51
+// with 4, 0.49 with 8; 64 images of 1024^2 with the aggregated key pass: 1.10, 1.13, 1.37),
+// and never more counters than the planes' bins would have needed, so the workspace does
+// not grow.
 constexpr int kMaxLog2Rep = 4;
-constexpr int64_t kBestCounters = 1ll << 16, kMostCounters = 1ll << 18;
+constexpr int64_t kManyRows = 1ll << 25;
+constexpr int64_t kBestCounters = 1ll << 16, kBestCountersManyRows = 1ll << 15, kMostCounters = 1ll << 18;
 // Counters are spread over cache lines where there are few of them: with the planes' bins,
 // 1.7e5 counters (1024^2, 23 planes) 0.52 -> 0.46 ms, but 5.2e5 (2048^2, 128 planes)
 // 1.28 -> 1.37 ms.
 constexpr int64_t kMaxSpread = 1ll << 18;
 
-BinShape bin_shape(const wproj_kernels *k, bool once = false) {
+// once_rows: rows of a single call, -1 for a kept or stable binning.
+BinShape bin_shape(const wproj_kernels *k, int64_t once_rows = -1) {
   BinShape B;
   B.tile = k->tile;
   B.log2_tile = 0;
@@ -253,13 +257,14 @@ BinShape bin_shape(const wproj_kernels *k, bool once = false) {
   B.n_tiles = (int64_t)k->geo.n_grids * B.ntx * B.nty;
   B.n_keys = B.n_tiles * B.kw;
   B.log2_rep = 0;
-  if (once && B.pack_sub && !B.stable) {
+  if (once_rows >= 0 && B.pack_sub && !B.stable) {
     const int64_t room = B.n_keys;
     B.kw = 1;
     B.n_keys = B.n_tiles;
+    const int64_t best = once_rows > kManyRows ? kBestCountersManyRows : kBestCounters;
     auto fits = [&](int r) {
       const int64_t c = B.n_keys << r;
-      return c <= room && (c <= kBestCounters || (r <= 2 && c <= kMostCounters));
+      return c <= room && (c <= best || (r <= 2 && c <= kMostCounters));
     };
     while (B.log2_rep < kMaxLog2Rep && fits(B.log2_rep + 1)) ++B.log2_rep;
   }
@@ -273,8 +278,9 @@ BinShape bin_shape(const wproj_kernels *k, bool once = false) {
 int64_t max_keys(const wproj_kernels *) { return (int64_t)0x7fffffffll; }
 
 // Lays the binning buffers out from `base` (nullptr: sizes only); returns total bytes.
-int64_t carve(const wproj_kernels *k, int64_t nvis, char *base, BinWorkspace &W) {
-  const BinShape B = bin_shape(k);
+// B: the shape with the planes in the key where they may be (bin_shape without once_rows), which
+// needs the most room.
+int64_t carve(const wproj_kernels *k, const BinShape &B, int64_t nvis, char *base, BinWorkspace &W) {
   const int64_t rec_bytes = k->params.precision == WPROJ_F64 ? sizeof(RecordF64) : sizeof(RecordF32);
   // a tile with r records gives ceil(r / chunk) <= r / chunk + 1 items, and at most
   // min(n_tiles, nvis) tiles hold records
@@ -289,22 +295,23 @@ int64_t carve(const wproj_kernels *k, int64_t nvis, char *base, BinWorkspace &W)
   // the record's tap word
   W.slots = (uint32_t *)take(4 * nvis * (B.pack_sub ? 3 : 4));
   W.rec = take(rec_bytes * nvis);
-  W.count = (uint32_t *)take(4 * ((B.n_counts + 255) & ~255ll));
+  const int64_t zero_from = off;
+  W.wslots = (double *)take(8 * kSlots * (int64_t)k->params.n_images);
+  W.cslots = (unsigned long long *)take(8 * 3 * kSlots);
+  W.order_cnt = (uint32_t *)take(4 * 2 * kOrderBuckets);
+  W.queues = (uint32_t *)take(4 * kQueues * kQueueStride);
+  W.zero_words = (off - zero_from) / 4;  // and the counters after them
+  W.count = (uint32_t *)take(4 * std::max(counter_words(B), counter_words(bin_shape(k, nvis))));
   W.offset = (uint32_t *)take(4 * (B.n_counts + 1));
-  W.nch = (uint32_t *)take(4 * B.n_tiles);
   W.choff = (uint32_t *)take(4 * (B.n_tiles + 1));
   W.items = (WorkItem *)take((int64_t)sizeof(WorkItem) * max_items);
   const int64_t digit_slots = B.stable ? radix_digit_slots(nvis) : 0;
-  W.scan_tmp = (uint32_t *)take(4 * scan_temp_words(std::max({B.n_counts, B.n_tiles, digit_slots})));
-  W.queues = (uint32_t *)take(4 * kQueues * kQueueStride);
+  W.scan_tmp = (uint32_t *)take(4 * std::max(scan_temp_words(std::max(B.n_counts, digit_slots)), work_temp_words(B.n_tiles)));
   W.order = (uint32_t *)take(4 * max_items);
-  W.order_cnt = (uint32_t *)take(4 * 2 * kOrderBuckets);
   W.max_items = max_items;
   const TileShape ts = tile_shape(k, B.tile);
   const int64_t cplx = k->params.precision == WPROJ_F64 ? 16 : 8;
   W.partial = take(max_items * (int64_t)ts.rows * ts.rows * cplx);
-  W.wslots = (double *)take(8 * kSlots * (int64_t)k->params.n_images);
-  W.cslots = (unsigned long long *)take(8 * 3 * kSlots);
   for (int i = 0; i < 2; ++i) {
     W.sort_keys[i] = B.stable ? (uint32_t *)take(4 * nvis) : nullptr;
     W.sort_vals[i] = B.stable ? (uint32_t *)take(4 * nvis) : nullptr;
@@ -342,12 +349,34 @@ int64_t workspace_bytes_for(const wproj_kernels *k, int64_t nvis) {
       tmp.plane_in_key = plane_in_key_for(k, tile);
       tmp.chunk = kTuneChunks[0];
       BinWorkspace W;
-      ws = std::max(ws, carve(&tmp, nvis, nullptr, W));
+      ws = std::max(ws, carve(&tmp, bin_shape(&tmp), nvis, nullptr, W));
     }
     BinWorkspace W;
-    ws = std::max(ws, carve(k, nvis, nullptr, W));
+    ws = std::max(ws, carve(k, bin_shape(k), nvis, nullptr, W));
   }
   return ws;
+}
+
+// Work-item length of a call: the handle's, or, where neither the caller nor the autotuner
+// chose one, down to kMinAutoChunk so that a call of few rows still gives each wavefront that
+// fits on the device an item (2e4 rows in FP64 on 256^2: gridder 99 us with items of 2048, of
+// which the busiest tile's runs alone, 25 with items of 128; 1024^2, 4e6 rows, support 9: 293
+// -> 188 us), as far
+// as the workspace that the autotuner's choices need holds the partial tiles.  With stable
+// bins the length stays as it is, since a reproducible grid's rounding follows it.
+constexpr int kMinAutoChunk = 128;
+BinShape call_shape(const wproj_kernels *k, int64_t nvis, BinWorkspace &W, char *base, bool once) {
+  BinShape full = bin_shape(k);
+  if (k->chunk_auto) {
+    const int64_t want = nvis / ((int64_t)k->n_cu * 32), limit = workspace_bytes_for(k, nvis);
+    for (full.chunk = kMinAutoChunk; full.chunk < k->chunk; full.chunk *= 2)
+      if (full.chunk >= want && carve(k, full, nvis, nullptr, W) <= limit) break;
+  }
+  carve(k, full, nvis, base, W);
+  if (!once) return full;
+  BinShape B = bin_shape(k, nvis);
+  B.chunk = full.chunk;
+  return B;
 }
 
 struct TuneKey {
@@ -467,6 +496,7 @@ int wproj_make_kernels(const wproj_params *params, void *stream, wproj_kernels *
     k->tile = 16;
   }
   if (params->chunk) k->chunk = params->chunk;
+  k->chunk_auto = params->chunk == 0 && !params->stable_bins;
   k->bin_aggregate = params->bin_aggregate;
   k->stable_bins = params->stable_bins;
 
@@ -663,12 +693,11 @@ int wproj_grid(const wproj_kernels *k, int64_t nvis, const double *uvw, const vo
   if (k->n_taps > (int64_t)kTapMask)
     return fail(WPROJ_EUNSUPPORTED, "kernel tables of %lld taps exceed the tiled gridder's 2^26",
                 (long long)k->n_taps);
-  const BinShape B = bin_shape(k, true);
+  BinWorkspace W;
+  const BinShape B = call_shape(k, nvis, W, (char *)workspace, true);
   if (B.n_keys >= max_keys(k))
     return fail(WPROJ_EUNSUPPORTED, "%lld bins (images x tiles) exceed the tiled gridder's 31-bit keys",
                 (long long)B.n_keys);
-  BinWorkspace W;
-  carve(k, nvis, (char *)workspace, W);
   {
     PhaseTimer pt(k, WPROJ_PHASE_BIN, s);
     HIP_TRY(launch_bin(k, B, nvis, uvw, vis, weight, image_offsets, weight_sum, counters, W, s));
@@ -713,6 +742,7 @@ int wproj_autotune(wproj_kernels *k, int64_t nvis, const double *uvw, const void
       k->chunk = it->second.chunk;
       k->bin_aggregate = it->second.bin_aggregate;
       k->plane_in_key = plane_in_key_for(k, k->tile);
+      k->chunk_auto = false;
       return WPROJ_OK;
     }
   }
@@ -730,11 +760,13 @@ int wproj_autotune(wproj_kernels *k, int64_t nvis, const double *uvw, const void
   const bool was_profiling = k->profiling;
   k->profiling = false;
   const TuneChoice start{k->tile, k->chunk, k->bin_aggregate};
+  const bool was_auto = k->chunk_auto;
   auto set = [&](const TuneChoice &c) {
     k->tile = c.tile;
     k->chunk = c.chunk;
     k->bin_aggregate = c.bin_aggregate;
     k->plane_in_key = plane_in_key_for(k, c.tile);
+    k->chunk_auto = false;
   };
   // one warm-up and one timed call of a candidate; on failure the handle is restored
   auto time_one = [&](const TuneChoice &c, float &ms) -> int {
@@ -752,6 +784,7 @@ int wproj_autotune(wproj_kernels *k, int64_t nvis, const double *uvw, const void
     }
     if (rc != WPROJ_OK) {
       set(start);
+      k->chunk_auto = was_auto;
       k->profiling = was_profiling;
     }
     return rc;
@@ -813,21 +846,20 @@ int wproj_degrid(const wproj_kernels *k, int64_t nvis, const double *uvw, const 
   if (k->n_taps > (int64_t)kTapMask)
     return fail(WPROJ_EUNSUPPORTED, "kernel tables of %lld taps exceed the tiled degridder's 2^26",
                 (long long)k->n_taps);
-  BinShape B = bin_shape(k, true);
+  BinWorkspace W;
+  BinShape B = call_shape(k, nvis, W, (char *)workspace, true);
   if (B.n_keys >= max_keys(k))
     return fail(WPROJ_EUNSUPPORTED, "%lld bins (images x tiles) exceed the tiled degridder's 31-bit keys",
                 (long long)B.n_keys);
-  BinWorkspace W;
-  carve(k, nvis, (char *)workspace, W);
   // records binned for the degridder's own tile layout: the gridder's pitch for the
   // one-tap-per-lane kernel, an odd pitch for the row-per-lane kernel
   if (!tap_lane_degrid(k, B)) B.pitch = degrid_pitch(k, B.tile);
   {
     PhaseTimer pt(k, WPROJ_PHASE_BIN, s);
-    HIP_TRY(launch_bin(k, B, nvis, uvw, nullptr, nullptr, image_offsets, nullptr, nullptr, W, s));
+    HIP_TRY(launch_bin(k, B, nvis, uvw, nullptr, nullptr, image_offsets, nullptr, nullptr, W, s, vis_out));
   }
   PhaseTimer pt(k, WPROJ_PHASE_DEGRID, s);
-  HIP_TRY(launch_tiled_degrid(k, B, W, model_grid, vis_out, nvis, s));
+  HIP_TRY(launch_tiled_degrid(k, B, W, model_grid, vis_out, nvis, false, s));
   return WPROJ_OK;
 }
 
@@ -951,13 +983,12 @@ int wproj_plan_create(const wproj_kernels *k, int64_t nvis, const double *uvw, c
   if (!p) return fail(WPROJ_ENOMEM, "plan allocation failed");
   p->k = k;
   p->nvis = nvis;
-  p->B = bin_shape(k);
+  p->B = call_shape(k, nvis, p->W, (char *)workspace, false);
   if (p->B.n_keys >= max_keys(k)) {
     const long long n_keys = (long long)p->B.n_keys;
     delete p;
     return fail(WPROJ_EUNSUPPORTED, "%lld bins exceed the tiled path's 31-bit keys", n_keys);
   }
-  carve(k, nvis, (char *)workspace, p->W);
   if (nvis > 0) {
     PhaseTimer pt(k, WPROJ_PHASE_BIN, (hipStream_t)stream);
     const hipError_t e = launch_bin(k, p->B, nvis, uvw, nullptr, weight, image_offsets, weight_sum,
@@ -1014,7 +1045,7 @@ int wproj_degrid_planned(const wproj_plan *p, const void *model_grid, void *vis_
   if (rc != WPROJ_OK) return rc;
   if (p->nvis == 0) return WPROJ_OK;
   PhaseTimer pt(p->k, WPROJ_PHASE_DEGRID, (hipStream_t)stream);
-  HIP_TRY(launch_tiled_degrid(p->k, p->B, p->W, model_grid, vis_out, p->nvis, (hipStream_t)stream));
+  HIP_TRY(launch_tiled_degrid(p->k, p->B, p->W, model_grid, vis_out, p->nvis, true, (hipStream_t)stream));
   return WPROJ_OK;
 }
 

@@ -93,7 +93,7 @@ __device__ inline uint32_t counter_of(const BinShape &B, uint32_t key, uint32_t 
 // different lines: with 8 counters per key side by side the key pass gained nothing from
 // them (1024^2 image, 4e6 rows: binning 0.67 ms, spread 0.24).
 __device__ inline int64_t counter_place(uint32_t c, int64_t n) {
-  return (int64_t)(c & 255u) * ((n + 255) >> 8) + (c >> 8);
+  return (int64_t)(c & 255u) * counter_column(n) + (c >> 8);
 }
 __device__ inline uint32_t *counter_at(const BinShape &B, uint32_t *count, uint32_t key, uint32_t block) {
   const uint32_t c = counter_of(B, key, block);
@@ -483,7 +483,8 @@ template <typename Real, typename Cplx, typename Rec, bool TAPWORD, int V>
 __global__ void __launch_bounds__(kBinBlock)
     scatter_kernel(BinShape B, int log2_span, int64_t nvis, const Cplx *__restrict__ vis,
                    const Real *__restrict__ wt, const uint32_t *__restrict__ slots,
-                   const uint32_t *__restrict__ offset, int S_fix, Rec *__restrict__ rec) {
+                   const uint32_t *__restrict__ offset, int S_fix, Rec *__restrict__ rec,
+                   Cplx *__restrict__ zero_out) {
   Rec r[V];
   uint32_t key[V];
   bool ok[V];
@@ -493,6 +494,8 @@ __global__ void __launch_bounds__(kBinBlock)
     j[i] = (int64_t)blockIdx.x * (kBinBlock * V) + i * kBinBlock + threadIdx.x;
     ok[i] = j[i] < nvis &&
             make_record<Real, Cplx, Rec, TAPWORD>(nvis, vis, wt, slots, S_fix, j[i], r[i], key[i]);
+    // a row that is not binned keeps a zero prediction
+    if (zero_out && j[i] < nvis && !ok[i]) zero_out[j[i]] = Cplx{};
   }
 #pragma unroll
   for (int i = 0; i < V; ++i)
@@ -541,13 +544,15 @@ __device__ inline int64_t radix_elem(int w, int i, int lane) {
   return (int64_t)blockIdx.x * kRadixTile + (int64_t)w * (64 * kRadixSteps) + i * 64 + lane;
 }
 
+template <typename Cplx>
 __global__ void __launch_bounds__(kBinBlock)
     sort_key_kernel(int64_t nvis, uint32_t n_keys, const uint32_t *__restrict__ slots,
-                    uint32_t *__restrict__ keys) {
+                    uint32_t *__restrict__ keys, Cplx *__restrict__ zero_out) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= nvis) return;
   const uint32_t kw = slots[nvis + j];
   keys[j] = kw != kInvalid ? kw & ~kFoldBit : n_keys;
+  if (zero_out && kw == kInvalid) zero_out[j] = Cplx{};  // as in scatter_kernel
 }
 
 // count[d * n_blocks + block] = elements of the block whose digit is d.
@@ -644,22 +649,25 @@ __global__ void __launch_bounds__(kBinBlock)
     rec[p] = r;
 }
 
-// Adds the per-slot partial weight sums and counters into the caller's outputs, in a
-// fixed slot order.
-__global__ void __launch_bounds__(256)
-    finalize_kernel(int n_images, const double *__restrict__ wslots,
-                    const unsigned long long *__restrict__ cslots, double *wsum,
-                    unsigned long long *counters) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (wsum && t < n_images) {
+// Adds the per-slot partial weight sums and counters into the caller's outputs, in a fixed
+// order: wavefront `which` of the launch takes image `which`, or a counter after the images.
+__device__ inline void finalize_wave(int which, int n_images, const double *__restrict__ wslots,
+                                     const unsigned long long *__restrict__ cslots, double *wsum,
+                                     unsigned long long *counters) {
+  const int lane = threadIdx.x & 63;
+  if (which < n_images) {
+    if (!wsum) return;
     double s = 0.0;
-    for (int k = 0; k < kSlots; ++k) s += wslots[(int64_t)t * kSlots + k];
-    wsum[t] += s;
-  }
-  if (counters && t < 3) {
-    unsigned long long c = 0;
-    for (int k = 0; k < kSlots; ++k) c += cslots[t * kSlots + k];
-    counters[t] += c;
+    for (int k = lane; k < kSlots; k += 64) s += wslots[(int64_t)which * kSlots + k];
+    s = wave_sum(s);
+    if (lane == 0) wsum[which] += s;
+  } else if (which < n_images + 3) {
+    if (!counters) return;
+    const int c = which - n_images;
+    unsigned long long s = 0;
+    for (int k = lane; k < kSlots; k += 64) s += cslots[c * kSlots + k];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) counters[c] += s;
   }
 }
 
@@ -776,80 +784,98 @@ __global__ void __launch_bounds__(kScanBlock)
   if (blockIdx.x == gridDim.x - 1 && t == 0) out[n] = before + total;
 }
 
-__global__ void __launch_bounds__(256)
-    chunk_count_kernel(const uint32_t *__restrict__ offset, int64_t n_tiles, int kw, int chunk,
-                       uint32_t *__restrict__ nch) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_tiles) return;
-  const uint32_t b = offset[t * kw], e = offset[(t + 1) * kw];
-  nch[t] = (e - b + (uint32_t)chunk - 1) / (uint32_t)chunk;
-}
-
-__global__ void __launch_bounds__(256)
-    chunk_emit_kernel(const uint32_t *__restrict__ offset, int64_t n_tiles, int kw, int chunk,
-                      const uint32_t *__restrict__ choff, WorkItem *__restrict__ items) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_tiles) return;
-  const uint32_t b = offset[t * kw], e = offset[(t + 1) * kw];
-  uint32_t o = choff[t];
-  for (uint32_t s = b; s < e; s += (uint32_t)chunk, ++o) {
-    WorkItem w;
-    w.tile = (uint32_t)t;
-    w.begin = s;
-    w.end = min(e, s + (uint32_t)chunk);
-    items[o] = w;
-  }
-}
-
-// Largest-first work order.  The queue of the gridding and degridding kernels hands
-// out work items in this order, so the long items start early and the short ones fill
-// the end of the launch instead of one long item running alone (the work list itself
-// stays in tile order, which the partial-tile reduce relies on).  Items are counted
-// into kOrderBuckets size classes and placed class by class; the order inside a class
-// follows the placement atomics, which changes only the schedule, not any result.
-__device__ inline int size_class(const WorkItem &w, int chunk) {
-  const uint32_t size = w.end - w.begin;  // 1..chunk
-  const uint32_t c = (uint32_t)(((uint64_t)((uint32_t)chunk - size) * kOrderBuckets) / (uint32_t)chunk);
+// ---- work list ----
+//
+// Tile t's records are cut into items of at most `chunk` records; items stand in tile order
+// (the partial-tile reduce relies on it), choff[t] being tile t's first.  A separate order
+// lists them largest first, by kOrderBuckets size classes, so that the gridding and
+// degridding kernels start the long items early and fill the end of the launch with short
+// ones; the order inside a class follows the placement atomics, which changes only the
+// schedule, not any result.  Two launches over blocks of 256 tiles: items and classes
+// counted (with the weight sums' finalize_wave in further blocks of the same launch), then
+// emitted.
+__device__ inline int size_class(uint32_t size, uint32_t chunk) {  // size 1..chunk
+  const uint32_t c = (uint32_t)(((uint64_t)(chunk - size) * kOrderBuckets) / chunk);
   return (int)min(c, (uint32_t)(kOrderBuckets - 1));
 }
 
-__global__ void __launch_bounds__(256)
-    order_count_kernel(const WorkItem *__restrict__ items, const uint32_t *__restrict__ n_items_ptr,
-                       int chunk, uint32_t *class_count) {
-  __shared__ uint32_t h[kOrderBuckets];
+__global__ void __launch_bounds__(kScanBlock)
+    work_count_kernel(const uint32_t *__restrict__ offset, int64_t n_tiles, int step, uint32_t chunk,
+                      unsigned tile_blocks, uint32_t *__restrict__ block_sums, uint32_t *class_count, int n_images,
+                      const double *__restrict__ wslots, const unsigned long long *__restrict__ cslots,
+                      double *wsum, unsigned long long *counters) {
+  if (blockIdx.x >= tile_blocks) {
+    finalize_wave((int)((blockIdx.x - tile_blocks) * (kScanBlock / 64) + (threadIdx.x >> 6)), n_images, wslots, cslots,
+                  wsum, counters);
+    return;
+  }
+  __shared__ uint32_t h[kOrderBuckets], sh[kScanBlock / 64];
   if (threadIdx.x < kOrderBuckets) h[threadIdx.x] = 0u;
   __syncthreads();
-  const uint32_t n = *n_items_ptr;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) atomicAdd(&h[size_class(items[i], chunk)], 1u);
-  __syncthreads();
+  uint32_t mine = 0, total;
+  const int64_t t = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
+  if (t < n_tiles) {
+    const uint32_t n = offset[(t + 1) * step] - offset[t * step];
+    const uint32_t full = n / chunk, rest = n - full * chunk;
+    if (full) atomicAdd(&h[0], full);
+    if (rest) atomicAdd(&h[size_class(rest, chunk)], 1u);
+    mine = full + (rest ? 1u : 0u);
+  }
+  block_exclusive_scan(mine, sh, total);  // its barriers also close the class counts
+  if (threadIdx.x == 0) block_sums[blockIdx.x] = total;
   if (threadIdx.x < kOrderBuckets && h[threadIdx.x]) atomicAdd(&class_count[threadIdx.x], h[threadIdx.x]);
 }
 
-// order[start of class c + cursor] = item; start of class c = items in classes < c.
-__global__ void __launch_bounds__(256)
-    order_place_kernel(const WorkItem *__restrict__ items, const uint32_t *__restrict__ n_items_ptr,
-                       int chunk, const uint32_t *__restrict__ class_count, uint32_t *cursor,
-                       uint32_t *__restrict__ order) {
-  __shared__ uint32_t h[kOrderBuckets], base[kOrderBuckets];
+// SELF as in scan_tiles_kernel.
+template <bool SELF>
+__global__ void __launch_bounds__(kScanBlock)
+    work_emit_kernel(const uint32_t *__restrict__ offset, int64_t n_tiles, int step, uint32_t chunk,
+                     const uint32_t *__restrict__ block_sums, const uint32_t *__restrict__ class_count,
+                     uint32_t *cursor, uint32_t *__restrict__ choff, WorkItem *__restrict__ items,
+                     uint32_t *__restrict__ order) {
+  __shared__ uint32_t h[kOrderBuckets], base[kOrderBuckets], sh[kScanBlock / 64];
   if (threadIdx.x < kOrderBuckets) h[threadIdx.x] = 0u;
   __syncthreads();
-  const uint32_t n = *n_items_ptr;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int c = 0;
-  uint32_t rank = 0;
-  if (i < n) {
-    c = size_class(items[i], chunk);
-    rank = atomicAdd(&h[c], 1u);
+  const int64_t t = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
+  uint32_t begin = 0, end = 0, total, before;
+  if (t < n_tiles) {
+    begin = offset[t * step];
+    end = offset[(t + 1) * step];
   }
-  __syncthreads();
+  const uint32_t full = (end - begin) / chunk, rest = end - begin - full * chunk;
+  if (full) atomicAdd(&h[0], full);
+  if (rest) atomicAdd(&h[size_class(rest, chunk)], 1u);
+  const uint32_t mine = full + (rest ? 1u : 0u);
+  if constexpr (SELF) {
+    uint32_t s = 0;
+    for (int64_t b = threadIdx.x; b < (int64_t)blockIdx.x; b += kScanBlock) s += block_sums[b];
+    block_exclusive_scan(s, sh, before);
+  } else {
+    before = block_sums[blockIdx.x];
+  }
+  uint32_t o = before + block_exclusive_scan(mine, sh, total);
   if (threadIdx.x < kOrderBuckets) {
     uint32_t start = 0;
     for (int k = 0; k < (int)threadIdx.x; ++k) start += class_count[k];
-    base[threadIdx.x] = h[threadIdx.x] ? start + atomicAdd(&cursor[threadIdx.x], h[threadIdx.x]) : 0u;
+    const uint32_t n = h[threadIdx.x];
+    base[threadIdx.x] = n ? start + atomicAdd(&cursor[threadIdx.x], n) : 0u;
+    h[threadIdx.x] = 0u;
   }
   __syncthreads();
-  if (i < n) order[base[c] + rank] = (uint32_t)i;
+  if (t < n_tiles) choff[t] = o;
+  if (full) {
+    const uint32_t place = base[0] + atomicAdd(&h[0], full);
+    for (uint32_t m = 0; m < full; ++m, ++o) {
+      items[o] = WorkItem{(uint32_t)t, begin + m * chunk, begin + (m + 1) * chunk};
+      order[place + m] = o;
+    }
+  }
+  if (rest) {
+    const int c = size_class(rest, chunk);
+    items[o] = WorkItem{(uint32_t)t, end - rest, end};
+    order[base[c] + atomicAdd(&h[c], 1u)] = o;
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) choff[n_tiles] = before + total;
 }
 
 template <typename Rec>
@@ -872,19 +898,20 @@ inline unsigned nblk(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); 
 // key (radix passes over the key's significant bits) and gathered in sorted order.
 template <typename Real, typename Cplx, typename Rec, bool TAPWORD>
 hipError_t place_records(const wproj_kernels *k, const BinShape &B, int64_t nvis, const void *vis, const void *wt,
-                         const BinWorkspace &W, int S_fix, hipStream_t s) {
+                         const BinWorkspace &W, int S_fix, void *zero_out, hipStream_t s) {
   const dim3 grid(nblk(nvis, kBinBlock)), block(kBinBlock);
   if (!B.stable) {
     const int log2_span = B.aggregate ? kLog2AggSpan : kLog2KeySpan;
     if (!TAPWORD && !B.aggregate)
       hipLaunchKernelGGL((scatter_kernel<Real, Cplx, Rec, TAPWORD, 2>), dim3(nblk(nvis, 2 * kBinBlock)), block, 0, s,
-                         B, log2_span, nvis, (const Cplx *)vis, (const Real *)wt, W.slots, W.offset, S_fix, (Rec *)W.rec);
+                         B, log2_span, nvis, (const Cplx *)vis, (const Real *)wt, W.slots, W.offset, S_fix, (Rec *)W.rec, (Cplx *)zero_out);
     else
       hipLaunchKernelGGL((scatter_kernel<Real, Cplx, Rec, TAPWORD, 1>), grid, block, 0, s, B, log2_span, nvis,
-                         (const Cplx *)vis, (const Real *)wt, W.slots, W.offset, S_fix, (Rec *)W.rec);
+                         (const Cplx *)vis, (const Real *)wt, W.slots, W.offset, S_fix, (Rec *)W.rec, (Cplx *)zero_out);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(sort_key_kernel, grid, block, 0, s, nvis, (uint32_t)B.n_keys, W.slots, W.sort_keys[0]);
+  hipLaunchKernelGGL((sort_key_kernel<Cplx>), grid, block, 0, s, nvis, (uint32_t)B.n_keys, W.slots, W.sort_keys[0],
+                     (Cplx *)zero_out);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // keys run from 0 to n_keys (not gridded)
@@ -921,6 +948,7 @@ hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s) {
 }
 
 int64_t scan_temp_words(int64_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
+int64_t work_temp_words(int64_t n_tiles) { return (n_tiles + kScanBlock - 1) / kScanBlock + 1; }
 
 int64_t radix_digit_slots(int64_t nvis) {
   return std::max<int64_t>(1, (nvis + kRadixTile - 1) / kRadixTile) * kRadixDigits;
@@ -960,14 +988,11 @@ hipError_t launch_plan_rows(const wproj_kernels *k, const BinShape &B, const Bin
 
 hipError_t launch_bin(const wproj_kernels *k, const BinShape &B, int64_t nvis, const double *uvw,
                       const void *vis, const void *wt, const int64_t *img_off, double *wsum,
-                      int64_t *counters, const BinWorkspace &W, hipStream_t s) {
+                      int64_t *counters, const BinWorkspace &W, hipStream_t s, void *zero_out) {
   const Geometry &G = k->geo;
-  hipError_t e = launch_fill_u32(W.count, (B.n_counts + 255) & ~255ll, 0u, s);
+  // counters, weight-sum and counter slots (bit pattern 0 is 0.0), size classes, queue heads
+  hipError_t e = launch_fill_u32((uint32_t *)W.wslots, W.zero_words + counter_words(B), 0u, s);
   if (e != hipSuccess) return e;
-  // zero the slot accumulators (bit pattern 0 is 0.0 and 0)
-  if ((e = launch_fill_u32((uint32_t *)W.wslots, 2 * kSlots * (int64_t)k->params.n_images, 0u, s)) != hipSuccess)
-    return e;
-  if ((e = launch_fill_u32((uint32_t *)W.cslots, 2 * 3 * kSlots, 0u, s)) != hipSuccess) return e;
   double *wpart = wsum ? W.wslots : nullptr;
   auto *cnt = counters ? W.cslots : nullptr;
   const dim3 key_grid(nblk(nvis, kBinBlock * kKeyVpt)), block(kBinBlock);
@@ -999,40 +1024,30 @@ hipError_t launch_bin(const wproj_kernels *k, const BinShape &B, int64_t nvis, c
       key_pass(float{}, std::false_type{});
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (wsum || counters) {
-    const int ni = k->params.n_images;
-    hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((std::max(ni, 3) + 255) / 256)), dim3(256), 0,
-                       s, ni, W.wslots, W.cslots, wsum, reinterpret_cast<unsigned long long *>(counters));
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
   e = B.spread ? exclusive_scan<true>(W.count, W.offset, B.n_counts, W.scan_tmp, s)
                : exclusive_scan<false>(W.count, W.offset, B.n_counts, W.scan_tmp, s);
   if (e != hipSuccess) return e;
   if (k->params.precision == WPROJ_F64)
-    e = tapword ? place_records<double, double2, RecordF64, true>(k, B, nvis, vis, wt, W, S_fix, s)
-                : place_records<double, double2, RecordF64, false>(k, B, nvis, vis, wt, W, S_fix, s);
+    e = tapword ? place_records<double, double2, RecordF64, true>(k, B, nvis, vis, wt, W, S_fix, zero_out, s)
+                : place_records<double, double2, RecordF64, false>(k, B, nvis, vis, wt, W, S_fix, zero_out, s);
   else if (!tapword && vis)  // W V records of a fixed support: no tap word (12 bytes)
-    e = place_records<float, float2, RecordF32P, false>(k, B, nvis, vis, wt, W, S_fix, s);
+    e = place_records<float, float2, RecordF32P, false>(k, B, nvis, vis, wt, W, S_fix, zero_out, s);
   else
-    e = tapword ? place_records<float, float2, RecordF32, true>(k, B, nvis, vis, wt, W, S_fix, s)
-                : place_records<float, float2, RecordF32, false>(k, B, nvis, vis, wt, W, S_fix, s);
+    e = tapword ? place_records<float, float2, RecordF32, true>(k, B, nvis, vis, wt, W, S_fix, zero_out, s)
+                : place_records<float, float2, RecordF32, false>(k, B, nvis, vis, wt, W, S_fix, zero_out, s);
   if (e != hipSuccess) return e;
-  // work list: per tile, ceil(records / chunk) items
-  hipLaunchKernelGGL(chunk_count_kernel, dim3(nblk(B.n_tiles, 256)), dim3(256), 0, s, W.offset,
-                     B.n_tiles, B.kw << B.log2_rep, B.chunk, W.nch);
+  const int ni = k->params.n_images, step = B.kw << B.log2_rep;
+  const unsigned tile_blocks = nblk(B.n_tiles, kScanBlock);
+  const unsigned fin_blocks = wsum || counters ? nblk(ni + 3, kScanBlock / 64) : 0;
+  hipLaunchKernelGGL(work_count_kernel, dim3(tile_blocks + fin_blocks), dim3(kScanBlock), 0, s, W.offset, B.n_tiles, step,
+                     (uint32_t)B.chunk, tile_blocks, W.scan_tmp, W.order_cnt, ni, W.wslots, W.cslots, wsum,
+                     reinterpret_cast<unsigned long long *>(counters));
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = launch_exclusive_scan(W.nch, W.choff, B.n_tiles, W.scan_tmp, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(chunk_emit_kernel, dim3(nblk(B.n_tiles, 256)), dim3(256), 0, s, W.offset,
-                     B.n_tiles, B.kw << B.log2_rep, B.chunk, W.choff, W.items);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  // largest-first order of the work items (their number is choff[n_tiles] <= max_items)
-  if ((e = launch_fill_u32(W.order_cnt, 2 * kOrderBuckets, 0u, s)) != hipSuccess) return e;
-  const uint32_t *n_items = W.choff + B.n_tiles;
-  hipLaunchKernelGGL(order_count_kernel, dim3(nblk(W.max_items, 256)), dim3(256), 0, s, W.items, n_items,
-                     B.chunk, W.order_cnt);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(order_place_kernel, dim3(nblk(W.max_items, 256)), dim3(256), 0, s, W.items, n_items,
-                     B.chunk, W.order_cnt, W.order_cnt + kOrderBuckets, W.order);
+  if (tile_blocks > kScanSelf)
+    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(1024), 0, s, W.scan_tmp, (int64_t)tile_blocks);
+  auto emit = tile_blocks > kScanSelf ? work_emit_kernel<false> : work_emit_kernel<true>;
+  hipLaunchKernelGGL(emit, dim3(tile_blocks), dim3(kScanBlock), 0, s, W.offset, B.n_tiles, step, (uint32_t)B.chunk,
+                     W.scan_tmp, W.order_cnt, W.order_cnt + kOrderBuckets, W.choff, W.items, W.order);
   return hipGetLastError();
 }
 

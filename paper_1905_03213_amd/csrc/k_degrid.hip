@@ -520,16 +520,18 @@ bool tap_lane_degrid(const wproj_kernels *k, const BinShape &B) {
 }
 
 hipError_t launch_tiled_degrid(const wproj_kernels *k, const BinShape &B, const BinWorkspace &W,
-                               const void *model_grid, void *vis_out, int64_t nvis, hipStream_t s) {
+                               const void *model_grid, void *vis_out, int64_t nvis, bool planned, hipStream_t s) {
   // the tile copy uses the row pitch the records' LDS offsets were binned with
   TileShape ts = tile_shape(k, B.tile);
   ts.pitch = B.pitch;
   ts.lds_bytes = (size_t)ts.rows * ts.pitch * (k->params.precision == WPROJ_F64 ? 16 : 8);
-  // rows that are dropped or belong to no image keep a zero prediction
-  const int64_t words = nvis * (k->params.precision == WPROJ_F64 ? 4 : 2);
-  hipError_t e = launch_fill_u32((uint32_t *)vis_out, words, 0u, s);
-  if (e != hipSuccess) return e;
-  if ((e = launch_fill_u32(W.queues, kQueues * kQueueStride, 0u, s)) != hipSuccess) return e;
+  if (planned) {
+    // rows that the plan does not hold get a zero prediction
+    const int64_t words = nvis * (k->params.precision == WPROJ_F64 ? 4 : 2);
+    hipError_t e = launch_fill_u32((uint32_t *)vis_out, words, 0u, s);
+    if (e != hipSuccess) return e;
+    if ((e = launch_fill_u32(W.queues, kQueues * kQueueStride, 0u, s)) != hipSuccess) return e;
+  }
   if (tap_lane_degrid(k, B)) return dispatch_tap_lane<float2, kMinFixedSupport>(k, B, ts, W, model_grid, vis_out, s);
   switch (k->params.precision) {
     case WPROJ_F64:

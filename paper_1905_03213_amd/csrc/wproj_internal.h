@@ -199,6 +199,7 @@ struct wproj_kernels {
   int tile = 16;            // tiled gridder tile side
   bool plane_in_key = true; // bin by (tile, plane) rather than tile alone
   int chunk = 2048;         // max records per gridder work item
+  bool chunk_auto = false;  // nobody chose chunk: calls of few rows take shorter items
   int bin_aggregate = 0;    // binning's count aggregation (wproj_params::bin_aggregate)
   int stable_bins = 0;      // records keep input order inside a bin (wproj_params::stable_bins)
   int n_cu = 256;           // compute units of the device
