@@ -262,11 +262,13 @@ typedef enum {
  * Transforms between grid and image; the DFTs are centred and unnormalised:
  *   IDFT(G)[y][x] = sum_{Y,X} G[Y][X] exp(+2 pi i ((X - n/2)(x - n/2) + (Y - n/2)(y - n/2))/n)
  *   DFT(I)[Y][X]  = sum_{y,x} I[y][x] exp(-2 pi i ((X - n/2)(x - n/2) + (Y - n/2)(y - n/2))/n)
- * (the paper's final IFFT, Sections 2.1-2.2; rocFFT does the 2D transforms).
+ * (the paper's final IFFT, Sections 2.1-2.2; for n a power of two from 128 to 4096 the
+ * library's own transforms, with the correction in the same passes; rocFFT's for other n,
+ * and for image -> grid in FP32 or with w-stacking).
  * GRID_TO_IMAGE*: grid's contents are destroyed (without w-stacking the image's real
  * transform takes the grid's Hermitian half spectrum, formed in the workspace, and
- * writes its output over the grid; with w-stacking each layer is transformed in place)
- * and image is written.  IMAGE_TO_GRID: image is read and grid is overwritten.
+ * rocFFT writes its output over the grid; with w-stacking the layers are transformed in
+ * place) and image is written.  IMAGE_TO_GRID: image is read and grid is overwritten.
  * weight_sum (float64 [n_images], device) is read only by GRID_TO_IMAGE; an image
  * whose sum is 0 is written as zeros (see wproj_check_weights).
  * Errors: WPROJ_EINVAL, WPROJ_EWORKSPACE, WPROJ_EFFT.
@@ -318,8 +320,8 @@ typedef enum {
   WPROJ_PHASE_BIN = 0,      /* key/count, scan, scatter, work list (tiled gridding) */
   WPROJ_PHASE_GRID = 1,     /* the LDS-tile gridder kernel (work-queue reset + gridder) */
   WPROJ_PHASE_PLAIN = 2,    /* the plain gridder kernel */
-  WPROJ_PHASE_FFT = 3,      /* rocFFT execution inside wproj_image */
-  WPROJ_PHASE_CORRECT = 4,  /* grid-correction / pre-correction kernel of wproj_image */
+  WPROJ_PHASE_FFT = 3,      /* the transforms inside wproj_image; the correction too where one pass does both */
+  WPROJ_PHASE_CORRECT = 4,  /* grid-correction / pre-correction kernel of wproj_image, where a pass of its own */
   WPROJ_PHASE_DEGRID = 5,   /* the degridder kernel */
   WPROJ_PHASE_REDUCE = 6,   /* adding the tile gridder's partial tiles into the grid */
   WPROJ_N_PHASES = 7

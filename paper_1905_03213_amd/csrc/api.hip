@@ -1,5 +1,5 @@
 // C ABI entry points: argument checking, handle construction (kernel tables, grid
-// correction, rocFFT plans) and dispatch to the kernel launchers.
+// correction, image transforms) and dispatch to the kernel launchers.
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -180,6 +180,7 @@ void destroy(wproj_kernels *k) {
   (void)hipFree(k->d_tab_off);
   (void)hipFree(k->d_tab);
   (void)hipFree(k->d_tab_pair);
+  (void)hipFree(k->d_twiddle);
   (void)hipFree(k->d_kappa);
   (void)hipFree(k->d_taper);
   delete k;
@@ -577,35 +578,49 @@ int wproj_make_kernels(const wproj_params *params, void *stream, wproj_kernels *
     HIP_TRY(launch_pair_table(k, s));
   }
 
-  // FFT plans (batched over images, in place, unnormalised)
-  std::call_once(g_fft_once, [] { g_fft_setup = rocfft_setup(); });
-  if (g_fft_setup != rocfft_status_success) return fail(WPROJ_EFFT, "rocfft_setup failed");
-  const size_t lengths[2] = {(size_t)n, (size_t)n};
-  const rocfft_precision fp =
-      params->precision == WPROJ_F64 ? rocfft_precision_double : rocfft_precision_single;
-  // one transform per grid: n_images of them, n_images x layers with w-stacking
-  if (rocfft_plan_create(&k->fft_inv, rocfft_placement_inplace,
-                         rocfft_transform_type_complex_inverse, fp, 2, lengths,
-                         (size_t)G.n_grids, nullptr) != rocfft_status_success ||
-      rocfft_plan_create(&k->fft_fwd, rocfft_placement_inplace,
-                         rocfft_transform_type_complex_forward, fp, 2, lengths,
-                         (size_t)G.n_grids, nullptr) != rocfft_status_success)
-    return fail(WPROJ_EFFT, "rocfft_plan_create failed for %dx%d x %d", n, n, G.n_grids);
-  size_t w1 = 0, w2 = 0;
-  rocfft_plan_get_work_buffer_size(k->fft_inv, &w1);
-  rocfft_plan_get_work_buffer_size(k->fft_fwd, &w2);
-  k->fft_work_bytes = std::max(w1, w2);
-  // grid -> image without w-stacking: the image is Re IFFT(G) = IFFT of G's Hermitian part,
-  // a complex-to-real transform of the half spectrum (half the work of the complex one).
-  // Out of place: the half spectrum in the workspace, the real output over the grid.
-  if (params->w_mode != WPROJ_W_STACK) {
-    if (rocfft_plan_create(&k->fft_c2r, rocfft_placement_notinplace, rocfft_transform_type_real_inverse, fp, 2,
-                           lengths, (size_t)G.n_grids, nullptr) != rocfft_status_success)
-      return fail(WPROJ_EFFT, "rocfft_plan_create (complex to real) failed for %dx%d x %d", n, n, G.n_grids);
-    const size_t real = params->precision == WPROJ_F64 ? 8 : 4;
-    k->herm_bytes = (size_t)G.n_grids * (size_t)n * (size_t)(n / 2 + 1) * 2 * real;
-    rocfft_plan_get_work_buffer_size(k->fft_c2r, &k->c2r_work_bytes);
-    k->fft_work_bytes = std::max(k->fft_work_bytes, (size_t)align_up((int64_t)k->herm_bytes) + k->c2r_work_bytes);
+  // FFTs (batched over images, unnormalised): the library's own where the side allows it, else
+  // rocFFT's, and those for image -> grid in FP32 or with w-stacking
+  const bool stack = params->w_mode == WPROJ_W_STACK, own = own_fft(n);
+  const size_t real = params->precision == WPROJ_F64 ? 8 : 4;
+  if (!stack) k->herm_bytes = (size_t)G.n_grids * (size_t)n * (size_t)(n / 2 + 1) * 2 * real;
+  if (own) {
+    const std::vector<double> w = twiddle_table(n);
+    const std::vector<float> wf(w.begin(), w.end());
+    if (hipMalloc(&k->d_twiddle, w.size() * real) != hipSuccess)
+      return fail(WPROJ_ENOMEM, "device allocation of the twiddle table failed");
+    const void *src = real == 8 ? (const void *)w.data() : (const void *)wf.data();
+    HIP_TRY(hipMemcpyAsync(k->d_twiddle, src, w.size() * real, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));  // the host copy ends here
+    k->fft_work_bytes = k->herm_bytes;
+  }
+  if (!own_image_to_grid(k)) {
+    std::call_once(g_fft_once, [] { g_fft_setup = rocfft_setup(); });
+    if (g_fft_setup != rocfft_status_success) return fail(WPROJ_EFFT, "rocfft_setup failed");
+    const size_t lengths[2] = {(size_t)n, (size_t)n};
+    const rocfft_precision fp = real == 8 ? rocfft_precision_double : rocfft_precision_single;
+    // one transform per grid: n_images of them, n_images x layers with w-stacking
+    auto plan = [&](rocfft_plan *p, rocfft_result_placement place, rocfft_transform_type type, size_t &work) {
+      if (rocfft_plan_create(p, place, type, fp, 2, lengths, (size_t)G.n_grids, nullptr) != rocfft_status_success)
+        return fail(WPROJ_EFFT, "rocfft_plan_create failed for %dx%d x %d", n, n, G.n_grids);
+      rocfft_plan_get_work_buffer_size(*p, &work);
+      return (int)WPROJ_OK;
+    };
+    size_t w_fwd = 0, w_inv = 0;
+    if ((rc = plan(&k->fft_fwd, rocfft_placement_inplace, rocfft_transform_type_complex_forward, w_fwd)) != WPROJ_OK)
+      return rc;
+    if (stack && !own &&
+        (rc = plan(&k->fft_inv, rocfft_placement_inplace, rocfft_transform_type_complex_inverse, w_inv)) != WPROJ_OK)
+      return rc;
+    k->fft_work_bytes = std::max({k->fft_work_bytes, w_fwd, w_inv});
+    // grid -> image without w-stacking: the image is Re IFFT(G) = IFFT of G's Hermitian part,
+    // a complex-to-real transform of the half spectrum (half the work of the complex one).
+    // Out of place: the half spectrum in the workspace, the real output over the grid.
+    if (!stack && !own) {
+      if ((rc = plan(&k->fft_c2r, rocfft_placement_notinplace, rocfft_transform_type_real_inverse,
+                     k->c2r_work_bytes)) != WPROJ_OK)
+        return rc;
+      k->fft_work_bytes = std::max(k->fft_work_bytes, (size_t)align_up((int64_t)k->herm_bytes) + k->c2r_work_bytes);
+    }
   }
 
   HIP_TRY(hipStreamSynchronize(s));
@@ -878,6 +893,14 @@ int wproj_image(const wproj_kernels *k, int direction, void *grid, void *image,
     return fail(WPROJ_EWORKSPACE, "workspace of %lld bytes given, %lld needed",
                 (long long)workspace_bytes, (long long)k->fft_work_bytes);
   hipStream_t s = (hipStream_t)stream;
+  if (k->d_twiddle && (direction != WPROJ_IMAGE_TO_GRID || own_image_to_grid(k))) {
+    PhaseTimer pt(k, WPROJ_PHASE_FFT, s);
+    if (direction == WPROJ_IMAGE_TO_GRID)
+      HIP_TRY(launch_image_to_grid(k, image, workspace, grid, s));
+    else
+      HIP_TRY(launch_grid_to_image(k, grid, workspace, image, direction == WPROJ_GRID_TO_IMAGE ? weight_sum : nullptr, s));
+    return WPROJ_OK;
+  }
   rocfft_execution_info info = nullptr;
   if (rocfft_execution_info_create(&info) != rocfft_status_success)
     return fail(WPROJ_EFFT, "rocfft_execution_info_create failed");

@@ -116,24 +116,6 @@ __global__ void __launch_bounds__(kPixThreads)
   }
 }
 
-// w-stacking: n - 1 at pixel (x, y), n = sqrt(1 - l^2 - m^2), l = (x - n/2) cell,
-// m = (y - n/2) cell; false outside the unit circle (no sky there: the layer factor is 0).
-__device__ inline bool n_minus_1(const Geometry &G, int x, int y, double &nm1) {
-#pragma clang fp contract(off)
-  const double l = ((double)x - (double)G.n / 2.0) * G.cell;
-  const double m = ((double)y - (double)G.n / 2.0) * G.cell;
-  const double r2 = l * l + m * m;
-  if (!(r2 < 1.0)) return false;
-  nm1 = sqrt(1.0 - r2) - 1.0;
-  return true;
-}
-
-// Layer centre w_l = -w_max + (l + 1/2) D, the same operations as the footprint rule.
-__device__ inline double layer_centre(const Geometry &G, int layer) {
-#pragma clang fp contract(off)
-  return -G.w_max + ((double)layer + 0.5) * G.layer_w;
-}
-
 // Grid -> image with w-stacking: for image i, Re(sum over layers l of
 // IDFT(G_{i,l})[y][x] exp(+2 pi i w_l (n - 1))) kappa(x) kappa(y) / sumW_i.  F holds the
 // unshifted inverse FFTs of the n_images L grids (layer fastest).

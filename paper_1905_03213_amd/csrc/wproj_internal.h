@@ -152,6 +152,24 @@ __device__ inline bool w_clamped(const Geometry &G, double w) {
   return (G.n_w > 1 || G.n_layers > 1) && fabs(w) > G.w_max;
 }
 
+// w-stacking: n - 1 at pixel (x, y), n = sqrt(1 - l^2 - m^2), l = (x - n/2) cell,
+// m = (y - n/2) cell; false outside the unit circle (no sky there: the layer factor is 0).
+__device__ inline bool n_minus_1(const Geometry &G, int x, int y, double &nm1) {
+#pragma clang fp contract(off)
+  const double l = ((double)x - (double)G.n / 2.0) * G.cell;
+  const double m = ((double)y - (double)G.n / 2.0) * G.cell;
+  const double r2 = l * l + m * m;
+  if (!(r2 < 1.0)) return false;
+  nm1 = sqrt(1.0 - r2) - 1.0;
+  return true;
+}
+
+// Layer centre w_l = -w_max + (l + 1/2) D, the same operations as the footprint rule.
+__device__ inline double layer_centre(const Geometry &G, int layer) {
+#pragma clang fp contract(off)
+  return -G.w_max + ((double)layer + 0.5) * G.layer_w;
+}
+
 // Image owning row j: the largest i with off[i] <= j, or -1 outside [off[0], off[n_images]).
 __device__ inline int image_of(const int64_t *off, int n_images, int64_t j) {
   if (off == nullptr) return 0;
@@ -190,6 +208,9 @@ struct wproj_kernels {
   size_t tap_bytes = 0;
   double *d_kappa = nullptr;
   double *d_taper = nullptr;
+  // twiddle factors of the image transforms of k_fft.hip (complex, the handle's precision);
+  // null for the sides that go through rocFFT
+  void *d_twiddle = nullptr;
   rocfft_plan fft_fwd = nullptr, fft_inv = nullptr;
   // grid -> image without w-stacking: complex-to-real inverse of the grid's Hermitian part
   // (herm_bytes of it at the start of the workspace, the plan's own work buffer after)
@@ -255,7 +276,19 @@ hipError_t launch_plain_degrid(const wproj_kernels *k, int64_t nvis, const doubl
 hipError_t launch_footprints(const wproj_kernels *k, int64_t nvis, const double *uvw,
                              const void *wt, int32_t *out, hipStream_t s);
 
-// Image-plane kernels around the FFTs.
+// Image transforms for sides that are powers of two from 128 to 4096 (k_fft.hip).  half:
+// n_images n (n/2 + 1) complex values of scratch (not read with w-stacking, whose layers are
+// transformed along x in place).  launch_image_to_grid: FP64 without w-stacking.
+bool own_fft(int n);
+inline bool own_image_to_grid(const wproj_kernels *k) {
+  return own_fft(k->params.n) && k->params.precision == WPROJ_F64 && k->params.w_mode != WPROJ_W_STACK;
+}
+std::vector<double> twiddle_table(int n);  // (re, im) pairs
+hipError_t launch_grid_to_image(const wproj_kernels *k, void *grid, void *half, void *image, const double *wsum,
+                                hipStream_t s);
+hipError_t launch_image_to_grid(const wproj_kernels *k, const void *image, void *half, void *grid, hipStream_t s);
+
+// Image-plane kernels around rocFFT's transforms.
 hipError_t launch_g2i_correct(const wproj_kernels *k, const void *fgrid, void *image,
                               const double *wsum, hipStream_t s);
 hipError_t launch_i2g_precorrect(const wproj_kernels *k, const void *image, void *grid,
