@@ -72,8 +72,7 @@ template <> struct Cx<double> { using T = double2; };
 // issued before the first is consumed, so up to kGroup memory latencies overlap per
 // wavefront.
 constexpr int kGroup = 8;
-// The same for the per-record-support path, whose table misses reach past L2 (cfg3's
-// 4096^2 rows: 4.03 ms with 8, 3.94 with 16, 4.72 with 32).
+// The same for the per-record-support path, whose table misses reach past L2.
 constexpr int kVarGroup = 16;
 
 // One tap of an FP32 or FP16 table loaded through a buffer resource (lane's byte offset
@@ -168,10 +167,9 @@ __global__ void __launch_bounds__(64 * kMaxWavesPerBlock)
     const WorkItem w = items[item];
     for (int i = lane; i < area; i += 64) acc[i] = C2{Real(0), Real(0)};
     const uint32_t n_rec = w.end - w.begin;
-    // Records arrive with one coalesced load a batch: 32 with a fixed support (lanes i and
-    // 32 + i hold record i), else 64.
+    // Records arrive with one coalesced load a batch (lanes i and 32 + i hold record i).
     constexpr bool kPaired = S > 0 && kPairedTab<Tab>;
-    constexpr uint32_t kBatch = S > 0 ? 32 : 64;
+    constexpr uint32_t kBatch = 32;
     const uint32_t slot = (uint32_t)lane & (kBatch - 1u);
     // Lanes past the last record load it again, so that no load hides behind a branch (the
     // compiler then knows how many are in flight); weigh gives them zero weight.
@@ -415,81 +413,160 @@ __global__ void __launch_bounds__(64 * kMaxWavesPerBlock)
         cur = next;
       }
     } else if constexpr (kHasTap<Rec> && std::is_same_v<Real, float>) {
-      // Per-record supports with FP32 arithmetic.  Records arrive 64 at a time (one
-      // coalesced load, readlane broadcasts).  A record with S <= 8 takes one pass, lane t
-      // tap t; its taps load one group of kVarGroup records ahead, at a wave-uniform scalar
-      // offset (the table carries 64 zero taps past its end, so lanes t >= S^2 of its last
-      // sub-kernel stay inside it).  The lane's cell offset follows the support and is
-      // recomputed only when the support changes (a tile's records come plane by plane).
-      // Larger supports take their passes as they go.
+      // Per-record supports with FP32 arithmetic: lane t handles taps t, 64 + t, ... of a
+      // record.  The lane's cells follow the support and are recomputed only when it changes (a
+      // tile's records come plane by plane).  A batch whose supports all take one pass (S <= 8)
+      // goes as with a fixed support: DPP broadcasts, taps loaded kVarGroup records ahead.  (Lanes
+      // t >= S^2 load taps of the next sub-kernel; past the table's end a load gives zero.)
+      // Other batches take kPasses passes, 2 (S <= 11) or 4 (S <= 16), their taps loaded
+      // kVarGroup/kPasses records ahead; supports beyond 16 load their taps as they go.
+      // 5.05e7 rows of S = 4 .. 16 on 4096^2 with an FP16 table: 1.84 ms; 3.94 with readlane
+      // broadcasts and no loads ahead for S > 8, whose rows, 7 in 100, took 1.4 ms of it.  Held
+      // to 128 registers (four wavefronts per SIMD instead of three) it spills: 2.01 ms.
       using Raw = typename TapRaw<Tab>::T;
-      int s_cur = 0, p_off = 0;
-      bool p_on = false;
-      auto set_support = [&](int Sn) {
-        // t / Sn by a float reciprocal: (t + 1/2) / Sn lies at least 1/(2 Sn) from an
-        // integer, far beyond the rounding of this product
-        const int kv = (int)(((float)lane + 0.5f) * (1.0f / (float)Sn));
-        p_on = lane < Sn * Sn;
-        p_off = kv * pitch + (lane - kv * Sn);
+      constexpr int kMaxPasses = 4;
+      uint32_t s_cur = 0, p_off[kMaxPasses];
+      bool p_on[kMaxPasses];
+      auto set_support = [&](uint32_t Sn) {
+        const float inv = 1.0f / (float)Sn;
+#pragma unroll
+        for (int q = 0; q < kMaxPasses; ++q) {
+          // t / Sn by a float reciprocal: (t + 1/2) / Sn lies at least 1/(2 Sn) from an
+          // integer, far beyond the rounding of this product
+          const uint32_t t = 64 * q + (uint32_t)lane, kv = (uint32_t)(((float)t + 0.5f) * inv);
+          p_on[q] = t < Sn * Sn;
+          p_off[q] = acc0 + (p_on[q] ? (kv * (uint32_t)pitch + (t - kv * Sn)) * 8u : 0u);
+        }
         s_cur = Sn;
       };
       const uint32_t vlane = (uint32_t)lane * (uint32_t)sizeof(Tab);
-      auto fetch_group = [&](const Rec &batch, int g, Raw (&dst)[kVarGroup]) {
+      struct Batch {  // records 16 g .. 16 g + 15, row-replicated: LDS and table offsets, W V
+        uint32_t cell[2], sub[2];
+        float wr[2], wi[2];
+        uint32_t support, change;  // lane i's support; bit i: it may differ from the one before
+      };
+      auto unpack = [&](const Rec &r) {
+        Batch o;
+        o.support = (r.tap >> kTapBits) + 1u;
+        // the support of the lane before, 0 for the first of each row of 16 lanes
+        const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)o.support, 0x111, 0xF, 0xF, false);
+        o.change = (uint32_t)__ballot(prev != o.support);
+        replicate16((r.lds & kLdsMask) * 8u, o.cell);
+        replicate16((r.tap & kTapMask) * (uint32_t)sizeof(Tab), o.sub);
+        replicate16(r.wr, o.wr);
+        replicate16(r.wi, o.wi);
+        return o;
+      };
+      auto fetch_group = [&](auto gi, Batch &bt, Raw (&dst)[kVarGroup]) {
+        constexpr int g = decltype(gi)::value;
+        dpp_ready(bt.cell[g], bt.sub[g], bt.wr[g], bt.wi[g]);
+        static_for<0, kVarGroup>([&](auto i) {
+          dst[decltype(i)::value] = TapRaw<Tab>::load(tab_rsrc, add_bcast<decltype(i)::value>(bt.sub[g], vlane), 0);
+        });
+      };
+      auto add_group = [&](auto gi, Batch &bt, const Raw (&src)[kVarGroup]) {
+        constexpr int g = decltype(gi)::value;
+        static_for<0, kVarGroup>([&](auto ii) {
+          constexpr int i = decltype(ii)::value;
+          if (bt.change >> (16 * g + i) & 1u) {
+            const uint32_t Sr = bcast(bt.support, 16 * g + i);
+            if (Sr != s_cur) set_support(Sr);
+            dpp_ready(bt.cell[g], bt.sub[g], bt.wr[g], bt.wi[g]);
+          }
+          const uint32_t at = add_bcast<i>(bt.cell[g], p_off[0]);
+          float2 v;
+          lds_read(at, v);
+          mac_bcast<i>(v, bt.wr[g], bt.wi[g], TapRaw<Tab>::value(src[i]));
+          if (p_on[0]) lds_write(at, v);
+        });
+      };
+      // records r (lane i: record i) in kPasses passes
+      auto add_passes = [&](auto passes, const Rec &r) {
+        constexpr int kPasses = decltype(passes)::value, kAhead = kVarGroup / kPasses;
+        auto fetch = [&](int j, Raw (&dst)[kAhead][kPasses]) {
 #pragma unroll
-        for (int i = 0; i < kVarGroup; ++i) {
-          const uint32_t tp = bcast(batch.tap, g * kVarGroup + i);
-          if ((tp >> kTapBits) < 8u) dst[i] = TapRaw<Tab>::load(tab_rsrc, vlane, (tp & kTapMask) * (uint32_t)sizeof(Tab));
+          for (int i = 0; i < kAhead; ++i) {
+            const uint32_t tp = bcast(r.tap, j + i), Sr = (tp >> kTapBits) + 1u;
+#pragma unroll
+            for (int q = 0; q < kPasses; ++q) {
+              const uint32_t t = 64 * q + (uint32_t)lane;
+              dst[i][q] = TapRaw<Tab>::load(tab_rsrc, t < Sr * Sr ? t * (uint32_t)sizeof(Tab) : 0u,
+                                            (tp & kTapMask) * (uint32_t)sizeof(Tab));
+            }
+          }
+        };
+        auto add = [&](int j, const Raw (&src)[kAhead][kPasses]) {
+#pragma unroll
+          for (int i = 0; i < kAhead; ++i) {
+            const uint32_t Sr = (bcast(r.tap, j + i) >> kTapBits) + 1u;
+            if (Sr != s_cur) set_support(Sr);
+            const uint32_t base = (bcast(r.lds, j + i) & kLdsMask) * 8u;
+            const float rwr = bcast(r.wr, j + i), rwi = bcast(r.wi, j + i);
+            float2 v[kPasses];
+#pragma unroll
+            for (int q = 0; q < kPasses; ++q) lds_read(base + p_off[q], v[q]);
+#pragma unroll
+            for (int q = 0; q < kPasses; ++q) {
+              const float2 t = TapRaw<Tab>::value(src[i][q]);
+              v[q].x = fmadd(rwr, t.x, v[q].x);
+              v[q].x = fmadd(-rwi, t.y, v[q].x);
+              v[q].y = fmadd(rwr, t.y, v[q].y);
+              v[q].y = fmadd(rwi, t.x, v[q].y);
+              if (p_on[q]) lds_write(base + p_off[q], v[q]);
+            }
+          }
+        };
+        Raw t0[kAhead][kPasses], t1[kAhead][kPasses];
+        fetch(0, t0);
+#pragma unroll 1
+        for (int j = 0; j < (int)kBatch; j += 2 * kAhead) {
+          fetch(j + kAhead, t1);
+          __builtin_amdgcn_sched_barrier(0);
+          add(j, t0);
+          if (j + 2 * kAhead < (int)kBatch) fetch(j + 2 * kAhead, t0);
+          __builtin_amdgcn_sched_barrier(0);
+          add(j + kAhead, t1);
         }
       };
-      auto accumulate_group = [&](const Rec &batch, int g, const Raw (&src)[kVarGroup]) {
-        bool large = false;
-#pragma unroll
-        for (int i = 0; i < kVarGroup; ++i) {
-          const int j = g * kVarGroup + i;
-          const uint32_t tp = bcast(batch.tap, j);
-          const int Sr = (int)(tp >> kTapBits) + 1;
-          if (Sr <= 8) {
-            if (Sr != s_cur) set_support(Sr);
-            const int base = (int)(bcast(batch.lds, j) & kLdsMask);
-            const Real rwr = bcast(batch.wr, j), rwi = bcast(batch.wi, j);
-            if (p_on) accumulate(acc, base + p_off, rwr, rwi, TapRaw<Tab>::value(src[i]));
-          } else {
-            large = true;
-          }
-        }
-        // records with S > 8 (several passes), their taps loaded as they go
-        if (large) {
+      Rec now, nxt;
+      C2 vnext;
+      load_batch(0, now);
+      load_rec(kBatch, nxt);
+      Batch cur = unpack(now);
+      Raw c0[kVarGroup], c1[kVarGroup];
+      fetch_group(std::integral_constant<int, 0>{}, cur, c0);
+      for (uint32_t b = 0; b < n_rec; b += kBatch) {
+        load_vis(nxt, vnext);
+        const bool one_pass = __ballot(cur.support > 8u) == 0;
+        if (one_pass) {
+          fetch_group(std::integral_constant<int, 1>{}, cur, c1);
+          __builtin_amdgcn_sched_barrier(0);
+          add_group(std::integral_constant<int, 0>{}, cur, c0);
+        } else if (__ballot(cur.support > 11u) == 0) {
+          add_passes(std::integral_constant<int, 2>{}, now);
+        } else if (__ballot(cur.support > 16u) == 0) {
+          add_passes(std::integral_constant<int, 4>{}, now);
+        } else {
 #pragma unroll 1
-          for (int i = 0; i < kVarGroup; ++i) {
-            const int j = g * kVarGroup + i;
-            const uint32_t tp = bcast(batch.tap, j);
-            const int Sr = (int)(tp >> kTapBits) + 1;
-            if (Sr <= 8) continue;
-            const uint32_t tb = tp & kTapMask;
-            const int base = (int)(bcast(batch.lds, j) & kLdsMask);
-            const Real rwr = bcast(batch.wr, j), rwi = bcast(batch.wi, j);
+          for (int j = 0; j < (int)kBatch; ++j) {
+            const uint32_t tp = bcast(now.tap, j);
+            const int Sr = (int)(tp >> kTapBits) + 1, base = (int)(bcast(now.lds, j) & kLdsMask);
+            const Real rwr = bcast(now.wr, j), rwi = bcast(now.wi, j);
             for (int t = lane; t < Sr * Sr; t += 64) {
               const int kv = t / Sr, ku = t - kv * Sr;
-              accumulate(acc, base + kv * pitch + ku, rwr, rwi, tab_load(tab, tb + (uint32_t)t));
+              accumulate(acc, base + kv * pitch + ku, rwr, rwi, tab_load(tab, (tp & kTapMask) + (uint32_t)t));
             }
           }
         }
-      };
-      Rec cur;
-      load_batch(0, cur);
-      for (uint32_t b = 0; b < n_rec; b += 64) {
-        Rec nxt;
-        const bool more = b + 64 < n_rec;
-        if (more) load_batch(b + 64, nxt);
-        Raw c0[kVarGroup], c1[kVarGroup];
-        fetch_group(cur, 0, c0);
-        for (int g = 0; g < 64 / kVarGroup; g += 2) {
-          fetch_group(cur, g + 1, c1);
-          accumulate_group(cur, g, c0);
-          if (g + 2 < 64 / kVarGroup) fetch_group(cur, g + 2, c0);
-          accumulate_group(cur, g + 1, c1);
-        }
-        if (more) cur = nxt;
+        // the next batch's first taps load during this one's last group
+        weigh(b + kBatch, nxt, vnext);
+        now = nxt;
+        Batch next = unpack(now);
+        load_rec(b + 2 * kBatch, nxt);
+        fetch_group(std::integral_constant<int, 0>{}, next, c0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (one_pass) add_group(std::integral_constant<int, 1>{}, cur, c1);
+        cur = next;
       }
     } else if constexpr (kHasTap<Rec>) {
       // General path (FP64; per-record support up to 32): records by wave-uniform loads,
