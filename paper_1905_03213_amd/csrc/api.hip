@@ -229,6 +229,11 @@ inline int64_t align_up(int64_t x) { return (x + kAlign - 1) / kAlign * kAlign; 
 // with 4, 0.49 with 8; 64 images of 1024^2 with the aggregated key pass: 1.10, 1.13, 1.37),
 // and never more counters than the planes' bins would have needed, so the workspace does
 // not grow.
+// Larger tables than this keep the planes: without their order the taps no longer come from the
+// 4 MB of an XCD's L2 (FP64 on 2048^2, 128 planes, call by tile and by plane: 18.9 MB of S = 12
+// 8.96 and 9.07 ms, 22.2 MB of S = 13 10.66 and 9.89, 33.6 MB of S = 16 17.1 and 15.0; FP32,
+// 16.8 MB of S = 16, 6.92 and 7.06).
+constexpr int64_t kMaxTileBinTable = 20000000;
 constexpr int kMaxLog2Rep = 4;
 constexpr int64_t kManyRows = 1ll << 25;
 constexpr int64_t kBestCounters = 1ll << 16, kBestCountersManyRows = 1ll << 15, kMostCounters = 1ll << 18;
@@ -258,7 +263,9 @@ BinShape bin_shape(const wproj_kernels *k, int64_t once_rows = -1) {
   B.n_tiles = (int64_t)k->geo.n_grids * B.ntx * B.nty;
   B.n_keys = B.n_tiles * B.kw;
   B.log2_rep = 0;
-  if (once_rows >= 0 && B.pack_sub && !B.stable) {
+  const int64_t table_bytes = n_sub * k->s_max * k->s_max *
+                              (k->params.precision == WPROJ_F64 ? 16 : k->params.precision == WPROJ_F32 ? 8 : 4);
+  if (once_rows >= 0 && B.pack_sub && !B.stable && table_bytes <= kMaxTileBinTable) {
     const int64_t room = B.n_keys;
     B.kw = 1;
     B.n_keys = B.n_tiles;
