@@ -372,11 +372,19 @@ int64_t workspace_bytes_for(const wproj_kernels *k, int64_t nvis) {
 // -> 188 us), as far
 // as the workspace that the autotuner's choices need holds the partial tiles.  With stable
 // bins the length stays as it is, since a reproducible grid's rounding follows it.
+// With a fixed support a CU's share is split between the wavefronts whose tile copies LDS holds:
+// of large copies few fit, and each costs more (FP64, S = 16, 16-cell tiles, 4e6 rows: 1.34 ms
+// with items of 512, 1.22 with 2048; S = 8: 0.484 with 512, 0.474 with 1024).  Elsewhere 32
+// ways, since a record takes longer there and long items end late (4e6 rows on 1024^2, FP64
+// supports 5 to 13: 0.57 ms with 512, 0.81 with 2048; FP32 18 to 22: 1.17 and 1.81).
 constexpr int kMinAutoChunk = 128;
+constexpr int64_t kCuLds = 160 * 1024;
 BinShape call_shape(const wproj_kernels *k, int64_t nvis, BinWorkspace &W, char *base, bool once) {
   BinShape full = bin_shape(k);
   if (k->chunk_auto) {
-    const int64_t want = nvis / ((int64_t)k->n_cu * 32), limit = workspace_bytes_for(k, nvis);
+    const int64_t held = std::max<int64_t>(1, kCuLds / (int64_t)tile_shape(k, k->tile).lds_bytes);
+    const int64_t waves = full.pack_sub ? std::min<int64_t>(32, held) : 32;
+    const int64_t want = nvis / (k->n_cu * waves), limit = workspace_bytes_for(k, nvis);
     for (full.chunk = kMinAutoChunk; full.chunk < k->chunk; full.chunk *= 2)
       if (full.chunk >= want && carve(k, full, nvis, nullptr, W) <= limit) break;
   }

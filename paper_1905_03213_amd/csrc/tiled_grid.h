@@ -481,7 +481,7 @@ __global__ void __launch_bounds__(64 * kMaxWavesPerBlock)
         });
       };
       // records r (lane i: record i) in kPasses passes
-      auto add_passes = [&](auto passes, const Rec &r) {
+      auto add_passes = [&](auto passes, const Rec &r, uint32_t left) {
         constexpr int kPasses = decltype(passes)::value, kAhead = kVarGroup / kPasses;
         auto fetch = [&](int j, Raw (&dst)[kAhead][kPasses]) {
 #pragma unroll
@@ -519,7 +519,7 @@ __global__ void __launch_bounds__(64 * kMaxWavesPerBlock)
         Raw t0[kAhead][kPasses], t1[kAhead][kPasses];
         fetch(0, t0);
 #pragma unroll 1
-        for (int j = 0; j < (int)kBatch; j += 2 * kAhead) {
+        for (int j = 0; j < (int)min(kBatch, left); j += 2 * kAhead) {
           fetch(j + kAhead, t1);
           __builtin_amdgcn_sched_barrier(0);
           add(j, t0);
@@ -543,12 +543,12 @@ __global__ void __launch_bounds__(64 * kMaxWavesPerBlock)
           __builtin_amdgcn_sched_barrier(0);
           add_group(std::integral_constant<int, 0>{}, cur, c0);
         } else if (__ballot(cur.support > 11u) == 0) {
-          add_passes(std::integral_constant<int, 2>{}, now);
+          add_passes(std::integral_constant<int, 2>{}, now, n_rec - b);
         } else if (__ballot(cur.support > 16u) == 0) {
-          add_passes(std::integral_constant<int, 4>{}, now);
+          add_passes(std::integral_constant<int, 4>{}, now, n_rec - b);
         } else {
 #pragma unroll 1
-          for (int j = 0; j < (int)kBatch; ++j) {
+          for (int j = 0; j < (int)min(kBatch, n_rec - b); ++j) {
             const uint32_t tp = bcast(now.tap, j);
             const int Sr = (int)(tp >> kTapBits) + 1, base = (int)(bcast(now.lds, j) & kLdsMask);
             const Real rwr = bcast(now.wr, j), rwi = bcast(now.wi, j);
@@ -563,7 +563,7 @@ __global__ void __launch_bounds__(64 * kMaxWavesPerBlock)
         now = nxt;
         Batch next = unpack(now);
         load_rec(b + 2 * kBatch, nxt);
-        fetch_group(std::integral_constant<int, 0>{}, next, c0);
+        if (__ballot(next.support > 8u) == 0) fetch_group(std::integral_constant<int, 0>{}, next, c0);
         __builtin_amdgcn_sched_barrier(0);
         if (one_pass) add_group(std::integral_constant<int, 1>{}, cur, c1);
         cur = next;
