@@ -281,6 +281,7 @@ struct BinWorkspace {
   WorkItem *items;     // [max_items]
   uint32_t *scan_tmp;  // scan_temp_words of the scans, work_temp_words(n_tiles)
   uint32_t *queues;    // [kQueues * kQueueStride] heads of the work queues
+  uint32_t n_queues = kQueues;  // of them used by tiled_degrid_kernel
   uint32_t *order;     // [max_items] work-item indices, largest items first
   uint32_t *order_cnt; // [2 * kOrderBuckets] per size class: item count, placement cursor
   int64_t max_items;   // capacity of items, order and partial
