@@ -264,7 +264,8 @@ typedef enum {
  *   DFT(I)[Y][X]  = sum_{y,x} I[y][x] exp(-2 pi i ((X - n/2)(x - n/2) + (Y - n/2)(y - n/2))/n)
  * (the paper's final IFFT, Sections 2.1-2.2; for n a power of two from 128 to 4096 the
  * library's own transforms, with the correction in the same passes; rocFFT's for other n,
- * and for image -> grid in FP32 or with w-stacking).
+ * for image -> grid in FP32 or with w-stacking, and for w-stacking images of fewer than
+ * 3 2^18 pixels in all).
  * GRID_TO_IMAGE*: grid's contents are destroyed (without w-stacking the image's real
  * transform takes the grid's Hermitian half spectrum, formed in the workspace, and
  * rocFFT writes its output over the grid; with w-stacking the layers are transformed in

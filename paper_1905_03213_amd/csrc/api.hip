@@ -595,7 +595,7 @@ int wproj_make_kernels(const wproj_params *params, void *stream, wproj_kernels *
 
   // FFTs (batched over images, unnormalised): the library's own where the side allows it, else
   // rocFFT's, and those for image -> grid in FP32 or with w-stacking
-  const bool stack = params->w_mode == WPROJ_W_STACK, own = own_fft(n);
+  const bool stack = params->w_mode == WPROJ_W_STACK, own = own_fft(*params);
   const size_t real = params->precision == WPROJ_F64 ? 8 : 4;
   if (!stack) k->herm_bytes = (size_t)G.n_grids * (size_t)n * (size_t)(n / 2 + 1) * 2 * real;
   if (own) {

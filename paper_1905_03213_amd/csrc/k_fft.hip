@@ -1,7 +1,7 @@
 // The image transforms for grid sides that are powers of two from 128 to 4096: 2D transforms
 // in two passes over memory, with what surrounds them (the Hermitian part, the grid
-// correction, the sum over w-stacking layers) done in the same passes.  Other sides go
-// through rocFFT (api.hip).
+// correction, the sum over w-stacking layers) done in the same passes.  Other sides, and few
+// small w-stacking layers (own_fft), go through rocFFT (api.hip).
 //
 // Bound by HBM: each pass reads and writes the data once, where rocFFT's passes and those of
 // the Hermitian part and the correction around them are five or more.  Transform and
@@ -547,7 +547,19 @@ template <typename F> hipError_t for_side(int n, F &&f) {
 
 }  // namespace
 
-bool own_fft(int n) { return n >= 128 && n <= 4096 && (n & (n - 1)) == 0; }
+// Which handles transform by themselves.  Without w-stacking: every side that has kernels.  With
+// it, the column pass goes through an image's layers one after the other in n/16 columns a
+// workgroup at the most, so few small images leave most of the chip idle, where rocFFT and a
+// pass over the pixels take all layers side by side.  rocFFT's way and here, us, for 12 FP32
+// layers: 22 and 42 for one image of 256^2, 37 and 47 for 4, 99 and 63 for 15; 49 and 76 for one
+// of 512^2, 120 and 89 for 3; 140 and 84 for one of 1024^2.  For one layer: 16 and 25 for one of
+// 512^2, 22 and 26 for 2, 28 and 27 for 3.  FP64 alike (3 images of 512^2: 33 and 31 with one
+// layer, 129 and 105 with 12).  The line is 3 2^18 pixels of images.
+constexpr int64_t kMinStackPixels = 3ll << 18;
+bool own_fft(const wproj_params &p) {
+  if (p.n < 128 || p.n > 4096 || (p.n & (p.n - 1)) != 0) return false;
+  return p.w_mode != WPROJ_W_STACK || (int64_t)p.n_images * p.n * p.n >= kMinStackPixels;
+}
 
 std::vector<double> twiddle_table(int n) {
   std::vector<double> w(2 * (size_t)twiddle_base(n, passes_of(n)));

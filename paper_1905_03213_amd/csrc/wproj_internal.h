@@ -276,12 +276,13 @@ hipError_t launch_plain_degrid(const wproj_kernels *k, int64_t nvis, const doubl
 hipError_t launch_footprints(const wproj_kernels *k, int64_t nvis, const double *uvw,
                              const void *wt, int32_t *out, hipStream_t s);
 
-// Image transforms for sides that are powers of two from 128 to 4096 (k_fft.hip).  half:
+// Image transforms for sides that are powers of two from 128 to 4096, with w-stacking for
+// enough pixels (k_fft.hip).  half:
 // n_images n (n/2 + 1) complex values of scratch (not read with w-stacking, whose layers are
 // transformed along x in place).  launch_image_to_grid: FP64 without w-stacking.
-bool own_fft(int n);
+bool own_fft(const wproj_params &p);
 inline bool own_image_to_grid(const wproj_kernels *k) {
-  return own_fft(k->params.n) && k->params.precision == WPROJ_F64 && k->params.w_mode != WPROJ_W_STACK;
+  return own_fft(k->params) && k->params.precision == WPROJ_F64 && k->params.w_mode != WPROJ_W_STACK;
 }
 std::vector<double> twiddle_table(int n);  // (re, im) pairs
 hipError_t launch_grid_to_image(const wproj_kernels *k, void *grid, void *half, void *image, const double *wsum,
