@@ -316,6 +316,7 @@ int64_t carve(const wproj_kernels *k, const BinShape &B, int64_t nvis, char *bas
   const int64_t digit_slots = B.stable ? radix_digit_slots(nvis) : 0;
   W.scan_tmp = (uint32_t *)take(4 * std::max(scan_temp_words(std::max(B.n_counts, digit_slots)), work_temp_words(B.n_tiles)));
   W.order = (uint32_t *)take(4 * max_items);
+  W.nvis = nvis;
   W.max_items = max_items;
   const TileShape ts = tile_shape(k, B.tile);
   const int64_t cplx = k->params.precision == WPROJ_F64 ? 16 : 8;
@@ -491,6 +492,7 @@ int wproj_make_kernels(const wproj_params *params, void *stream, wproj_kernels *
   const int m = params->kernel_image_size;
   k->supp_host = supp;
   k->s_max = *std::max_element(supp.begin(), supp.end());
+  k->s_min = *std::min_element(supp.begin(), supp.end());
   k->uniform_support = std::all_of(supp.begin(), supp.end(), [&](int v) { return v == supp[0]; });
   k->tab_off_host.assign(n_w + 1, 0);
   for (int p = 0; p < n_w; ++p)

@@ -474,9 +474,11 @@ hipError_t launch_one(const wproj_kernels *k, const BinShape &B, const TileShape
   e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * wpb, lds);
   if (e != hipSuccess) return e;
   if (per_cu < 1) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(k->n_cu * per_cu)), dim3(64 * wpb), lds, s, k->geo, B,
+  const unsigned blocks = (unsigned)(k->n_cu * per_cu);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * wpb), lds, s, k->geo, B,
                      ts.pitch, ts.rows, (const Tab *)k->d_tab, (const Rec *)W.rec,
-                     W.items, W.order, W.choff + B.n_tiles, W.queues, std::min<uint32_t>(W.n_queues, (unsigned)(k->n_cu * per_cu)),
+                     W.items, W.order, W.choff + B.n_tiles, W.queues,
+                     queue_count(k, kDegridQueueRule, W, blocks, blocks),
                      (const C2 *)model, (C2 *)out);
   return hipGetLastError();
 }
@@ -533,19 +535,13 @@ hipError_t launch_tiled_degrid(const wproj_kernels *k, const BinShape &B, const 
     if ((e = launch_fill_u32(W.queues, kQueues * kQueueStride, 0u, s)) != hipSuccess) return e;
   }
   if (tap_lane_degrid(k, B)) return dispatch_tap_lane<float2, kMinFixedSupport>(k, B, ts, W, model_grid, vis_out, s);
-  // Large supports over many rows take one queue: its head is far from busy then, and items
-  // handed out strictly in order share tables in L2 (4.0e6 rows, FP64, S = 14, tile 32: 3.11 ms
-  // with 16 queues, 2.93 with one; S = 12 alike).  2.5e5 rows of S = 16: 0.166 ms with 16, 0.178
-  // with one.
-  BinWorkspace V = W;
-  if (k->s_max > 12 && nvis > (1 << 20)) V.n_queues = 1;
   switch (k->params.precision) {
     case WPROJ_F64:
-      return dispatch<double, RecordF64, double2>(k, B, ts, V, model_grid, vis_out, s);
+      return dispatch<double, RecordF64, double2>(k, B, ts, W, model_grid, vis_out, s);
     case WPROJ_F32:
-      return dispatch<float, RecordF32, float2>(k, B, ts, V, model_grid, vis_out, s);
+      return dispatch<float, RecordF32, float2>(k, B, ts, W, model_grid, vis_out, s);
     default:
-      return dispatch<float, RecordF32, half2c>(k, B, ts, V, model_grid, vis_out, s);
+      return dispatch<float, RecordF32, half2c>(k, B, ts, W, model_grid, vis_out, s);
   }
 }
 

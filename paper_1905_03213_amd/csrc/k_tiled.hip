@@ -147,6 +147,14 @@ TileShape tile_shape(const wproj_kernels *k, int tile) {
   return t;
 }
 
+uint32_t queue_count(const wproj_kernels *k, const QueueRule &rule, const BinWorkspace &W, int64_t workgroups,
+                     int64_t workers) {
+  const int64_t taps = (int64_t)k->s_min * k->s_min * (int64_t)k->tap_bytes;
+  const int64_t takes = W.max_items + workers;
+  if (taps >= rule.tap_bytes && W.nvis * taps >= takes * rule.take_bytes) return 1;
+  return (uint32_t)std::min<int64_t>(kQueues, workgroups);
+}
+
 int degrid_pitch(const wproj_kernels *k, int tile) { return (tile + k->s_max - 1) | 1; }
 
 hipError_t launch_tiled_grid(const wproj_kernels *k, const BinShape &B, const BinWorkspace &W,

@@ -610,6 +610,8 @@ hipError_t launch_one(const wproj_kernels *k, const BinShape &B, const TileShape
   if (e != hipSuccess) return e;
   if (per_cu < 1) return hipErrorInvalidConfiguration;
   const unsigned blocks = (unsigned)(k->n_cu * per_cu);
+  const QueueRule &rule = S > 0 ? kFixedGridQueueRule : kGeneralGridQueueRule;
+  const uint32_t n_queues = queue_count(k, rule, W, blocks, (int64_t)blocks * wpb);
   const int wave_lds = (int)(ts.lds_bytes / (2 * sizeof(Real)));
   // the paired fixed-support kernels read the pair-ordered table
   constexpr bool paired = S > 0 && kPairedTab<Tab>;
@@ -619,8 +621,7 @@ hipError_t launch_one(const wproj_kernels *k, const BinShape &B, const TileShape
   const int64_t tab_entries = paired ? n_sub * k->pair_stride : k->n_taps;
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * wpb), lds, s, k->geo, B, ts.pitch,
                      ts.rows, wave_lds, tab, (uint32_t)(tab_entries * sizeof(Tab)),
-                     (const Rec *)W.rec, W.items, W.order, W.choff + B.n_tiles, W.queues,
-                     std::min<uint32_t>(kQueues, blocks), (typename Cx<Real>::T *)W.partial, (const typename Cx<Real>::T *)vis);
+                     (const Rec *)W.rec, W.items, W.order, W.choff + B.n_tiles, W.queues, n_queues, (typename Cx<Real>::T *)W.partial, (const typename Cx<Real>::T *)vis);
   return hipGetLastError();
 }
 

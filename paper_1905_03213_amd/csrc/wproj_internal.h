@@ -220,6 +220,7 @@ struct wproj_kernels {
   int tile = 16;            // tiled gridder tile side
   bool plane_in_key = true; // bin by (tile, plane) rather than tile alone
   int chunk = 2048;         // max records per gridder work item
+  int s_min = 0;            // smallest support
   bool chunk_auto = false;  // nobody chose chunk: calls of few rows take shorter items
   int bin_aggregate = 0;    // binning's count aggregation (wproj_params::bin_aggregate)
   int stable_bins = 0;      // records keep input order inside a bin (wproj_params::stable_bins)

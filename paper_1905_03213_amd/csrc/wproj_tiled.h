@@ -32,7 +32,9 @@ constexpr int kOrderBuckets = 16;
 // for the 2.6e5 tiles of 64 images of 1024^2 (16-cell tiles; 1.1 ms with 8, 16 or 32 heads,
 // 1.14 with 128), and 0.42 ms instead of 0.28 for 1e7 rows on 16 layers of 2048^2.  Queues
 // of their own for the small items, or a first item by the worker's number, measured slower
-// (1.46 against 1.38 ms on 5.6e7 records).  Heads lie 128 bytes apart.
+// (1.46 against 1.38 ms on 5.6e7 records), and so did workers that go on to another queue
+// when theirs is empty (up to 50 us more, for the failed atomics of a launch's end).  Heads lie
+// 128 bytes apart.
 constexpr uint32_t kQueues = 16;
 constexpr uint32_t kQueueStride = 32;
 struct WorkQueue {
@@ -42,8 +44,29 @@ struct WorkQueue {
   // one lane's call: the next item's place in the order (none is left when it is past the end)
   __device__ uint32_t next() { return atomicAdd(head, 1u) * n_queues + q; }
 };
-// LDS of a compute unit
-constexpr size_t kCuLds = 160 * 1024;
+// With large sub-kernels one queue is better where its head is not busy: items are then handed
+// out strictly in order, and items that run side by side share tables in the caches (16 queues
+// drift apart).  Its cost is 9 ns for each item and each worker's last try, its gain a part of
+// the time that the taps take, so the rule is the taps' bytes per take.  One queue's time over
+// 16 queues', by kernel (least sub-kernel and bytes a take):
+//   row-per-lane degridder  1536 B, 288 KB: FP64 S = 14 on 1024^2, 1.0e6 rows (420 KB) 0.97,
+//     2048^2, 1.6e7 rows 0.97, 1.0e6 rows (170 KB) 1.01; S = 11 and 12, tile 32, 4.0e6 rows 0.95;
+//     FP32 S = 16 0.98, on 64 images of 512^2 (118 KB) 0.99, S = 13 on 64 of 1024^2 (22 KB) 1.13;
+//     smaller sub-kernels 1.00 to 1.1;
+//   FP64 gridder            3072 B, 580 KB: S = 16 on 2048^2, 4.0e6 rows (790 KB) 0.92, 1.0e6
+//     rows (210 KB) 1.14; S = 14 0.95 and 1.20; S = 12 1.01 at best, and no FP32 support gains;
+//   general gridder         2048 B, 40 KB: FP64 S = 18 0.88 to 0.99, FP32 S = 20 0.92 to 0.98, but
+//     1.03 and 1.08 for 2.1e4 rows on 1024^2 (19 and 12 KB).
+// Per-plane supports count with their smallest, since most rows lie at small |w| (supports 4 to
+// 16 on 2048^2, degridding a plan of 4.0e6 rows: FP32 392 us with one queue, 367 with 16).
+struct QueueRule {
+  int64_t tap_bytes, take_bytes;
+};
+constexpr QueueRule kDegridQueueRule{1536, 288 << 10}, kFixedGridQueueRule{3072, 580 << 10},
+    kGeneralGridQueueRule{2048, 40 << 10};
+struct BinWorkspace;
+uint32_t queue_count(const wproj_kernels *k, const QueueRule &rule, const BinWorkspace &W, int64_t workgroups,
+                     int64_t workers);
 
 // Partial accumulators per image (weight sums) and per counter, spread by block index.
 constexpr int kSlots = 256;
@@ -281,9 +304,9 @@ struct BinWorkspace {
   WorkItem *items;     // [max_items]
   uint32_t *scan_tmp;  // scan_temp_words of the scans, work_temp_words(n_tiles)
   uint32_t *queues;    // [kQueues * kQueueStride] heads of the work queues
-  uint32_t n_queues = kQueues;  // of them used by tiled_degrid_kernel
   uint32_t *order;     // [max_items] work-item indices, largest items first
   uint32_t *order_cnt; // [2 * kOrderBuckets] per size class: item count, placement cursor
+  int64_t nvis;        // rows of the call
   int64_t max_items;   // capacity of items, order and partial
   void *partial;       // [max_items][rows][rows] complex: each work item's accumulated tile
   // wslots, cslots, order_cnt, queues and count follow each other and are cleared together at
