@@ -234,6 +234,21 @@ inline int64_t align_up(int64_t x) { return (x + kAlign - 1) / kAlign * kAlign; 
 // 8.96 and 9.07 ms, 22.2 MB of S = 13 10.66 and 9.89, 33.6 MB of S = 16 17.1 and 15.0; FP32,
 // 16.8 MB of S = 16, 6.92 and 7.06).
 constexpr int64_t kMaxTileBinTable = 20000000;
+// The row-per-lane degridder with supports above 8 gains less from the shorter binning and loses
+// more, since the wavefronts of an item then share no plane's taps: its limit is lower, and
+// lower still for tiles of 32 cells and more, of which a CU holds fewer copies.  A degridding
+// call's time with planes over its time by tile, 2.5e5 to 1.6e7 rows on 1024^2 to 4096^2.  T = 32:
+// 96 planes, FP32 S = 16 (12.6 MB) 0.92 to 0.98, FP64 S = 12 (14.2 MB) 0.95 to 0.99, FP32 S = 12
+// (7.1 MB) 0.95 to 1.02, FP64 S = 9 (8.0 MB) 0.98 to 1.06, FP16 S = 16 (6.3 MB) 1.02 to 1.07; 128
+// planes, FP32 S = 12 (9.4 MB) 0.93, S = 14 (12.8 MB) 0.92, FP64 S = 11 (15.9 MB) 0.93; 24 planes
+// (under 4 MB) 1.02 to 1.4.  T = 16: FP32 S = 16 of 96 planes (12.6 MB) 0.94 to 1.01, of 128 (16.8
+// MB) 0.96, FP64 S = 12 of 96 (14.2 MB) 0.97 to 1.03, S = 14 of 64 (12.8 MB) 1.00 to 1.03, FP32
+// S = 14 of 64 (7.3 MB) 1.00 to 1.04.  Many images, whose rows come with one channel each and so
+// without runs that tile bins would join, keep the planes for tiles of 32 in any case (32 planes,
+// S = 9 and 13: 64 images of 512^2 0.90 and 0.91, 256 of 256^2 0.85 and 0.89, 64 of 1024^2 0.99
+// and 0.97, but 4 of 1024^2 1.20 and 1.05; T = 16 0.98 to 1.04).
+constexpr int64_t kMaxTileBinTableRows[2] = {12500000, 9000000};  // tiles of 16, of 32 and more
+constexpr int kManyImages = 16;
 constexpr int kMaxLog2Rep = 4;
 constexpr int64_t kManyRows = 1ll << 25;
 constexpr int64_t kBestCounters = 1ll << 16, kBestCountersManyRows = 1ll << 15, kMostCounters = 1ll << 18;
@@ -243,7 +258,7 @@ constexpr int64_t kBestCounters = 1ll << 16, kBestCountersManyRows = 1ll << 15, 
 constexpr int64_t kMaxSpread = 1ll << 18;
 
 // once_rows: rows of a single call, -1 for a kept or stable binning.
-BinShape bin_shape(const wproj_kernels *k, int64_t once_rows = -1) {
+BinShape bin_shape(const wproj_kernels *k, int64_t once_rows = -1, bool degrid = false) {
   BinShape B;
   B.tile = k->tile;
   B.log2_tile = 0;
@@ -265,7 +280,10 @@ BinShape bin_shape(const wproj_kernels *k, int64_t once_rows = -1) {
   B.log2_rep = 0;
   const int64_t table_bytes = n_sub * k->s_max * k->s_max *
                               (k->params.precision == WPROJ_F64 ? 16 : k->params.precision == WPROJ_F32 ? 8 : 4);
-  if (once_rows >= 0 && B.pack_sub && !B.stable && table_bytes <= kMaxTileBinTable) {
+  int64_t most_bytes = kMaxTileBinTable;
+  if (degrid && k->s_max > 8)
+    most_bytes = B.tile >= 32 && k->params.n_images >= kManyImages ? 0 : kMaxTileBinTableRows[B.tile >= 32];
+  if (once_rows >= 0 && B.pack_sub && !B.stable && table_bytes <= most_bytes) {
     const int64_t room = B.n_keys;
     B.kw = 1;
     B.n_keys = B.n_tiles;
@@ -380,7 +398,8 @@ int64_t workspace_bytes_for(const wproj_kernels *k, int64_t nvis) {
 // supports 5 to 13: 0.57 ms with 512, 0.81 with 2048; FP32 18 to 22: 1.17 and 1.81).
 constexpr int kMinAutoChunk = 128;
 constexpr int64_t kCuLds = 160 * 1024;
-BinShape call_shape(const wproj_kernels *k, int64_t nvis, BinWorkspace &W, char *base, bool once) {
+enum class Binning { kGrid, kDegrid, kPlan };  // of a single call, or kept
+BinShape call_shape(const wproj_kernels *k, int64_t nvis, BinWorkspace &W, char *base, Binning what) {
   BinShape full = bin_shape(k);
   if (k->chunk_auto) {
     const int64_t held = std::max<int64_t>(1, kCuLds / (int64_t)tile_shape(k, k->tile).lds_bytes);
@@ -390,8 +409,8 @@ BinShape call_shape(const wproj_kernels *k, int64_t nvis, BinWorkspace &W, char 
       if (full.chunk >= want && carve(k, full, nvis, nullptr, W) <= limit) break;
   }
   carve(k, full, nvis, base, W);
-  if (!once) return full;
-  BinShape B = bin_shape(k, nvis);
+  if (what == Binning::kPlan) return full;
+  BinShape B = bin_shape(k, nvis, what == Binning::kDegrid);
   B.chunk = full.chunk;
   return B;
 }
@@ -726,7 +745,7 @@ int wproj_grid(const wproj_kernels *k, int64_t nvis, const double *uvw, const vo
     return fail(WPROJ_EUNSUPPORTED, "kernel tables of %lld taps exceed the tiled gridder's 2^26",
                 (long long)k->n_taps);
   BinWorkspace W;
-  const BinShape B = call_shape(k, nvis, W, (char *)workspace, true);
+  const BinShape B = call_shape(k, nvis, W, (char *)workspace, Binning::kGrid);
   if (B.n_keys >= max_keys(k))
     return fail(WPROJ_EUNSUPPORTED, "%lld bins (images x tiles) exceed the tiled gridder's 31-bit keys",
                 (long long)B.n_keys);
@@ -879,7 +898,7 @@ int wproj_degrid(const wproj_kernels *k, int64_t nvis, const double *uvw, const 
     return fail(WPROJ_EUNSUPPORTED, "kernel tables of %lld taps exceed the tiled degridder's 2^26",
                 (long long)k->n_taps);
   BinWorkspace W;
-  BinShape B = call_shape(k, nvis, W, (char *)workspace, true);
+  BinShape B = call_shape(k, nvis, W, (char *)workspace, Binning::kDegrid);
   if (B.n_keys >= max_keys(k))
     return fail(WPROJ_EUNSUPPORTED, "%lld bins (images x tiles) exceed the tiled degridder's 31-bit keys",
                 (long long)B.n_keys);
@@ -1023,7 +1042,7 @@ int wproj_plan_create(const wproj_kernels *k, int64_t nvis, const double *uvw, c
   if (!p) return fail(WPROJ_ENOMEM, "plan allocation failed");
   p->k = k;
   p->nvis = nvis;
-  p->B = call_shape(k, nvis, p->W, (char *)workspace, false);
+  p->B = call_shape(k, nvis, p->W, (char *)workspace, Binning::kPlan);
   if (p->B.n_keys >= max_keys(k)) {
     const long long n_keys = (long long)p->B.n_keys;
     delete p;

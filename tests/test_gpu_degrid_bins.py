@@ -1,0 +1,48 @@
+"""Single degridding calls whose bins keep the planes (large tables, and many images with tiles of
+32) and whose bins are whole tiles, on both sides of the rule, against the FP64 oracle."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_1905_03213_amd as W
+from gpu_util import CDT, rel_max
+from oracle import cref
+from oracle import wproj_ref as R
+
+pytestmark = pytest.mark.gpu
+
+# sums of up to 256 taps: 256 roundings of 6e-8 stay below 2e-5 of the peak
+TOL = {"f64": 1e-12, "f32": 2e-5}
+
+
+@pytest.mark.parametrize("prec,S,planes,images,tile", [
+    ("f32", 16, 96, 1, 16), ("f32", 16, 95, 1, 16),      # 12.58 and 12.45 MB of taps
+    ("f64", 12, 62, 1, 32), ("f64", 12, 61, 1, 32),      # 9.14 and 8.99 MB
+    ("f32", 9, 5, 16, 32), ("f32", 9, 5, 15, 32),
+    ("f64", 9, 5, 16, 64), ("f32", 8, 5, 16, 32),
+])
+def test_degrid_bins(prec, S, planes, images, tile):
+    n, nvis = 128, 40000
+    params = dict(n=n, cell_rad=0.02 / n, n_wplanes=planes, w_max=80.0, support=S, oversample=8, kernel_image_size=32,
+                  precision=prec, n_images=images, algorithm="tiled", tile=tile)
+    plan = R.Plan(params)
+    tabs = R.kernel_tables(plan)
+    rng = np.random.default_rng(planes + images)
+    cells = n / 2 + rng.standard_normal((nvis, 2)) * n / 6  # some footprints leave the grid
+    uvw = np.concatenate([(cells - n / 2) / 0.02, rng.uniform(-90, 90, (nvis, 1))], axis=1)
+    off = None
+    if images > 1:  # rows before the first and after the last image, and an empty image
+        off = np.sort(rng.integers(11, nvis - 11, images + 1))
+        off[2] = off[1]
+    k = W.make_kernels(params)
+    M = rng.standard_normal((images, n, n)) + 1j * rng.standard_normal((images, n, n))
+    model = torch.as_tensor(M).to(CDT[prec])
+    ref = cref.degrid(plan, tabs, uvw, model.to(torch.complex128).numpy(), off, nthreads=8)
+    out = torch.full((nvis,), 7.0, dtype=CDT[prec], device="cuda")
+    W.degrid(k, torch.as_tensor(uvw).cuda(), model.cuda(), out,
+             image_offsets=None if off is None else torch.as_tensor(off).cuda())
+    got = out.to(torch.complex128).cpu().numpy()
+    assert np.all(got[ref == 0] == 0)
+    assert rel_max(got, ref) < TOL[prec]
+    k.free()
