@@ -396,7 +396,15 @@ int64_t workspace_bytes_for(const wproj_kernels *k, int64_t nvis) {
 // with items of 512, 1.22 with 2048; S = 8: 0.484 with 512, 0.474 with 1024).  Elsewhere 32
 // ways, since a record takes longer there and long items end late (4e6 rows on 1024^2, FP64
 // supports 5 to 13: 0.57 ms with 512, 0.81 with 2048; FP32 18 to 22: 1.17 and 1.81).
-constexpr int kMinAutoChunk = 128;
+// A single degridding call with a fixed support up to 8 in FP32 arithmetic gives each of four
+// workgroups that a CU holds half an item, and no item less than the 512 records of its eight
+// wavefronts' batches: its records take so little time that the copies of a tile for a few of
+// them each are what counts.  Call with the gridder's length and with this, support 8, 64 planes,
+// 16-cell tiles: 1.0e5 rows on 256^2 47 and 42 us, 5.1e5 102 and 82, 2.0e6 198 and 179, on 1024^2
+// 191 and 171, on 2048^2 243 and 232; 2.0e4 rows and, on 1024^2, 1.0e5 the same.  With larger
+// supports and in FP64 no length from 256 to 2048 is more than 5 % faster than the gridder's for
+// 5.1e5 and 2.0e6 rows.
+constexpr int kMinAutoChunk = 128, kMinDegridChunk = 512;
 constexpr int64_t kCuLds = 160 * 1024;
 enum class Binning { kGrid, kDegrid, kPlan };  // of a single call, or kept
 BinShape call_shape(const wproj_kernels *k, int64_t nvis, BinWorkspace &W, char *base, Binning what) {
@@ -404,7 +412,10 @@ BinShape call_shape(const wproj_kernels *k, int64_t nvis, BinWorkspace &W, char 
   if (k->chunk_auto) {
     const int64_t held = std::max<int64_t>(1, kCuLds / (int64_t)tile_shape(k, k->tile).lds_bytes);
     const int64_t waves = full.pack_sub ? std::min<int64_t>(32, held) : 32;
-    const int64_t want = nvis / (k->n_cu * waves), limit = workspace_bytes_for(k, nvis);
+    const bool light = full.pack_sub && k->s_max <= 8 && k->params.precision != WPROJ_F64;
+    const int64_t want = what == Binning::kDegrid && light ? std::max<int64_t>(kMinDegridChunk, nvis / (2 * k->n_cu))
+                                                           : nvis / (k->n_cu * waves);
+    const int64_t limit = workspace_bytes_for(k, nvis);
     for (full.chunk = kMinAutoChunk; full.chunk < k->chunk; full.chunk *= 2)
       if (full.chunk >= want && carve(k, full, nvis, nullptr, W) <= limit) break;
   }

@@ -1,4 +1,5 @@
-"""Single degridding calls whose bins keep the planes (large tables, and many images with tiles of
+"""Single degridding calls with work items of every length from the shortest to the longest, and
+calls whose bins keep the planes (large tables, and many images with tiles of
 32) and whose bins are whole tiles, on both sides of the rule, against the FP64 oracle."""
 
 import numpy as np
@@ -45,4 +46,28 @@ def test_degrid_bins(prec, S, planes, images, tile):
     got = out.to(torch.complex128).cpu().numpy()
     assert np.all(got[ref == 0] == 0)
     assert rel_max(got, ref) < TOL[prec]
+    k.free()
+
+
+@pytest.mark.parametrize("prec", ["f32", "f32_f16table"])
+@pytest.mark.parametrize("S", [3, 8])
+@pytest.mark.parametrize("nvis", [1, 511, 513, 4100, 270000, 530001, 1100000])
+def test_degrid_items(nvis, S, prec):
+    n = 96
+    params = dict(n=n, cell_rad=0.02 / n, n_wplanes=3, w_max=80.0, support=S, oversample=8 if S == 8 else 4,
+                  kernel_image_size=32, precision=prec, n_images=1, algorithm="tiled")
+    plan = R.Plan(params)
+    tabs = R.kernel_tables(plan)
+    rng = np.random.default_rng(nvis)
+    # half of the rows in one tile
+    cells = n / 2 + rng.standard_normal((nvis, 2)) * np.where(rng.random((nvis, 1)) < 0.5, 2.0, n / 6)
+    uvw = np.concatenate([(cells - n / 2) / 0.02, rng.uniform(-90, 90, (nvis, 1))], axis=1)
+    k = W.make_kernels(params)
+    M = rng.standard_normal((1, n, n)) + 1j * rng.standard_normal((1, n, n))
+    model = torch.as_tensor(M).to(CDT[prec])
+    ref = cref.degrid(plan, tabs, uvw, model.to(torch.complex128).numpy(), nthreads=8)
+    out = torch.full((nvis,), 7.0, dtype=CDT[prec], device="cuda")
+    W.degrid(k, torch.as_tensor(uvw).cuda(), model.cuda(), out)
+    # FP16 taps carry 5e-4 each
+    assert rel_max(out.to(torch.complex128).cpu().numpy(), ref) < (2e-5 if prec == "f32" else 1e-3)
     k.free()
