@@ -224,11 +224,18 @@ inline int64_t align_up(int64_t x) { return (x + kAlign - 1) / kAlign * kAlign; 
 // Fewer bins are busier, so a bin has several counters, a block of the key pass using one of
 // them.  2^16 counters in all measured best for 4e6 rows on 1024^2 (0.22 ms, 0.24 with half
 // as many), 2^15 for the 6.5e7 rows (1.06 ms, 1.11 with 2^16, 1.09 with 2^14, 1.91 with one a
-// bin), whose scattered record writes gain from fewer open ends.  A bin gets at least 4
+// bin), whose scattered record writes gain from fewer open ends; from 8.1e6 to 3.2e7 rows on
+// 1024^2 to 4096^2 whole calls with either are within 1 %.  A bin gets at least 4
 // while 2^18 hold them (1e7 rows on 16 layers of 2048^2, 65536 bins: 0.72 ms with 1, 0.51
 // with 4, 0.49 with 8; 64 images of 1024^2 with the aggregated key pass: 1.10, 1.13, 1.37),
 // and never more counters than the planes' bins would have needed, so the workspace does
-// not grow.
+// not grow.  More than 16 a bin are for few tiles with many rows (call of 2.0e6 rows on 256^2
+// with 16 and up to 64: tiles of 16 265 and 223 us, of 32 700 and 230, of 64 1626 and 457; with
+// the planes 404, 535 and 1193); beyond one scan tile's 4096 counters they need 16 rows each (1.0e5
+// rows on 256^2, tiles of 16: 68 us with 4096, 69 to 71 with more; 5.1e5: 142 and 127).  Where the
+// planes allow fewer than 1024 counters, neighbouring planes' rows spread better over them than
+// the blocks do (8 planes, 1.0e5 to 2.0e6 rows, with planes over by tile: 512 counters 0.92 to
+// 0.98, 128 0.88 to 0.95; 2048 1.19 to 1.5).
 // Larger tables than this keep the planes: without their order the taps no longer come from the
 // 4 MB of an XCD's L2 (FP64 on 2048^2, 128 planes, call by tile and by plane: 18.9 MB of S = 12
 // 8.96 and 9.07 ms, 22.2 MB of S = 13 10.66 and 9.89, 33.6 MB of S = 16 17.1 and 15.0; FP32,
@@ -249,7 +256,8 @@ constexpr int64_t kMaxTileBinTable = 20000000;
 // and 0.97, but 4 of 1024^2 1.20 and 1.05; T = 16 0.98 to 1.04).
 constexpr int64_t kMaxTileBinTableRows[2] = {12500000, 9000000};  // tiles of 16, of 32 and more
 constexpr int kManyImages = 16;
-constexpr int kMaxLog2Rep = 4;
+constexpr int kMaxLog2Rep = 8, kLog2RepAnyRows = 4;
+constexpr int64_t kFewCounters = 1 << 10, kScanTileCounters = 1 << 12, kRowsPerCounter = 16;
 constexpr int64_t kManyRows = 1ll << 25;
 constexpr int64_t kBestCounters = 1ll << 16, kBestCountersManyRows = 1ll << 15, kMostCounters = 1ll << 18;
 // Counters are spread over cache lines where there are few of them: with the planes' bins,
@@ -285,14 +293,19 @@ BinShape bin_shape(const wproj_kernels *k, int64_t once_rows = -1, bool degrid =
     most_bytes = B.tile >= 32 && k->params.n_images >= kManyImages ? 0 : kMaxTileBinTableRows[B.tile >= 32];
   if (once_rows >= 0 && B.pack_sub && !B.stable && table_bytes <= most_bytes) {
     const int64_t room = B.n_keys;
-    B.kw = 1;
-    B.n_keys = B.n_tiles;
     const int64_t best = once_rows > kManyRows ? kBestCountersManyRows : kBestCounters;
     auto fits = [&](int r) {
-      const int64_t c = B.n_keys << r;
+      const int64_t c = B.n_tiles << r;
+      if (r > kLog2RepAnyRows && c > kScanTileCounters && c * kRowsPerCounter > once_rows) return false;
       return c <= room && (c <= best || (r <= 2 && c <= kMostCounters));
     };
-    while (B.log2_rep < kMaxLog2Rep && fits(B.log2_rep + 1)) ++B.log2_rep;
+    int rep = 0;
+    while (rep < kMaxLog2Rep && fits(rep + 1)) ++rep;
+    if (room >= kFewCounters) {
+      B.kw = 1;
+      B.n_keys = B.n_tiles;
+      B.log2_rep = rep;
+    }
   }
   B.n_counts = B.n_keys << B.log2_rep;
   B.spread = B.n_counts <= kMaxSpread;
