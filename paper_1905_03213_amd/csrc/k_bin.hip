@@ -793,7 +793,7 @@ __global__ void __launch_bounds__(kScanBlock)
 // ones; the order inside a class follows the placement atomics, which changes only the
 // schedule, not any result.  Two launches over blocks of 256 tiles: items and classes
 // counted (with the weight sums' finalize_wave in further blocks of the same launch), then
-// emitted.
+// emitted (and the queue heads cleared).
 __device__ inline int size_class(uint32_t size, uint32_t chunk) {  // size 1..chunk
   const uint32_t c = (uint32_t)(((uint64_t)(chunk - size) * kOrderBuckets) / chunk);
   return (int)min(c, (uint32_t)(kOrderBuckets - 1));
@@ -832,7 +832,7 @@ __global__ void __launch_bounds__(kScanBlock)
     work_emit_kernel(const uint32_t *__restrict__ offset, int64_t n_tiles, int step, uint32_t chunk,
                      const uint32_t *__restrict__ block_sums, const uint32_t *__restrict__ class_count,
                      uint32_t *cursor, uint32_t *__restrict__ choff, WorkItem *__restrict__ items,
-                     uint32_t *__restrict__ order) {
+                     uint32_t *__restrict__ order, uint32_t *__restrict__ queues) {
   __shared__ uint32_t h[kOrderBuckets], base[kOrderBuckets], sh[kScanBlock / 64];
   if (threadIdx.x < kOrderBuckets) h[threadIdx.x] = 0u;
   __syncthreads();
@@ -875,7 +875,10 @@ __global__ void __launch_bounds__(kScanBlock)
     items[o] = WorkItem{(uint32_t)t, end - rest, end};
     order[base[c] + atomicAdd(&h[c], 1u)] = o;
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) choff[n_tiles] = before + total;
+  if (blockIdx.x == gridDim.x - 1) {
+    if (threadIdx.x == 0) choff[n_tiles] = before + total;
+    for (uint32_t i = threadIdx.x; i < kQueues * kQueueStride; i += kScanBlock) queues[i] = 0u;
+  }
 }
 
 template <typename Rec>
@@ -990,7 +993,7 @@ hipError_t launch_bin(const wproj_kernels *k, const BinShape &B, int64_t nvis, c
                       const void *vis, const void *wt, const int64_t *img_off, double *wsum,
                       int64_t *counters, const BinWorkspace &W, hipStream_t s, void *zero_out) {
   const Geometry &G = k->geo;
-  // counters, weight-sum and counter slots (bit pattern 0 is 0.0), size classes, queue heads
+  // counters, weight-sum and counter slots (bit pattern 0 is 0.0), size classes
   hipError_t e = launch_fill_u32((uint32_t *)W.wslots, W.zero_words + counter_words(B), 0u, s);
   if (e != hipSuccess) return e;
   double *wpart = wsum ? W.wslots : nullptr;
@@ -1047,7 +1050,7 @@ hipError_t launch_bin(const wproj_kernels *k, const BinShape &B, int64_t nvis, c
     hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(1024), 0, s, W.scan_tmp, (int64_t)tile_blocks);
   auto emit = tile_blocks > kScanSelf ? work_emit_kernel<false> : work_emit_kernel<true>;
   hipLaunchKernelGGL(emit, dim3(tile_blocks), dim3(kScanBlock), 0, s, W.offset, B.n_tiles, step, (uint32_t)B.chunk,
-                     W.scan_tmp, W.order_cnt, W.order_cnt + kOrderBuckets, W.choff, W.items, W.order);
+                     W.scan_tmp, W.order_cnt, W.order_cnt + kOrderBuckets, W.choff, W.items, W.order, W.queues);
   return hipGetLastError();
 }
 
