@@ -371,6 +371,7 @@ int64_t carve(const wproj_kernels *k, const BinShape &B, int64_t nvis, char *bas
 // records' 14-bit LDS offset can address.
 constexpr int kTuneTiles[] = {16, 32, 64};
 constexpr int kTuneChunks[] = {1024, 2048, 4096, 8192, 16384};
+constexpr int kDefaultChunk = 2048;
 
 bool plane_in_key_for(const wproj_kernels *k, int tile) {
   const int64_t nt = (k->params.n + tile - 1) / tile;
@@ -402,7 +403,7 @@ int64_t workspace_bytes_for(const wproj_kernels *k, int64_t nvis) {
 }
 
 // Work-item length of a call: the handle's, or, where neither the caller nor the autotuner
-// chose one, down to kMinAutoChunk so that a call of few rows still gives each wavefront that
+// chose one for so few rows, down to kMinAutoChunk so that a call of few rows still gives each wavefront that
 // fits on the device an item (2e4 rows in FP64 on 256^2: gridder 99 us with items of 2048, of
 // which the busiest tile's runs alone, 25 with items of 128; 1024^2, 4e6 rows, support 9: 293
 // -> 188 us), as far
@@ -426,7 +427,7 @@ constexpr int64_t kCuLds = 160 * 1024;
 enum class Binning { kGrid, kDegrid, kPlan };  // of a single call, or kept
 BinShape call_shape(const wproj_kernels *k, int64_t nvis, BinWorkspace &W, char *base, Binning what) {
   BinShape full = bin_shape(k);
-  if (k->chunk_auto) {
+  if (nvis < k->chunk_rows) {
     const int64_t held = std::max<int64_t>(1, kCuLds / (int64_t)tile_shape(k, k->tile).lds_bytes);
     const int64_t waves = full.pack_sub ? std::min<int64_t>(32, held) : 32;
     const bool light = full.pack_sub && k->s_max <= 8 && k->params.precision != WPROJ_F64;
@@ -453,10 +454,22 @@ struct TuneKey {
   }
 };
 std::mutex g_tune_mu;
+// by_rows: the work-item length that the untuned handle takes (call_shape), at most chunk
 struct TuneChoice {
   int tile, chunk, bin_aggregate;
+  bool by_rows;
 };
 std::map<TuneKey, TuneChoice> g_tune_cache;
+
+// log2_nvis: of the rows that the choice was timed with, rounded down
+void apply(wproj_kernels *k, const TuneChoice &c, int log2_nvis) {
+  k->tile = c.tile;
+  k->chunk = c.chunk;
+  k->bin_aggregate = c.bin_aggregate;
+  k->plane_in_key = plane_in_key_for(k, c.tile);
+  // a reproducible grid's rounding follows the length
+  k->chunk_rows = k->stable_bins ? 0 : c.by_rows ? INT64_MAX : 1ll << log2_nvis;
+}
 
 }  // namespace
 
@@ -561,7 +574,7 @@ int wproj_make_kernels(const wproj_params *params, void *stream, wproj_kernels *
     k->tile = 16;
   }
   if (params->chunk) k->chunk = params->chunk;
-  k->chunk_auto = params->chunk == 0 && !params->stable_bins;
+  k->chunk_rows = params->chunk == 0 && !params->stable_bins ? INT64_MAX : 0;
   k->bin_aggregate = params->bin_aggregate;
   k->stable_bins = params->stable_bins;
 
@@ -817,11 +830,7 @@ int wproj_autotune(wproj_kernels *k, int64_t nvis, const double *uvw, const void
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune_cache.find(key);
     if (it != g_tune_cache.end()) {
-      k->tile = it->second.tile;
-      k->chunk = it->second.chunk;
-      k->bin_aggregate = it->second.bin_aggregate;
-      k->plane_in_key = plane_in_key_for(k, k->tile);
-      k->chunk_auto = false;
+      apply(k, it->second, lg);
       return WPROJ_OK;
     }
   }
@@ -838,18 +847,11 @@ int wproj_autotune(wproj_kernels *k, int64_t nvis, const double *uvw, const void
   } eg{e0, e1};
   const bool was_profiling = k->profiling;
   k->profiling = false;
-  const TuneChoice start{k->tile, k->chunk, k->bin_aggregate};
-  const bool was_auto = k->chunk_auto;
-  auto set = [&](const TuneChoice &c) {
-    k->tile = c.tile;
-    k->chunk = c.chunk;
-    k->bin_aggregate = c.bin_aggregate;
-    k->plane_in_key = plane_in_key_for(k, c.tile);
-    k->chunk_auto = false;
-  };
+  const TuneChoice start{k->tile, k->chunk, k->bin_aggregate, false};
+  const int64_t start_rows = k->chunk_rows;
   // one warm-up and one timed call of a candidate; on failure the handle is restored
   auto time_one = [&](const TuneChoice &c, float &ms) -> int {
-    set(c);
+    apply(k, c, lg);
     int rc = wproj_grid(k, nvis, uvw, vis, weight, image_offsets, scratch_grid, nullptr, nullptr,
                         workspace, workspace_bytes, stream);
     if (rc == WPROJ_OK) {
@@ -862,35 +864,44 @@ int wproj_autotune(wproj_kernels *k, int64_t nvis, const double *uvw, const void
         rc = fail(WPROJ_EHIP, "event timing failed");
     }
     if (rc != WPROJ_OK) {
-      set(start);
-      k->chunk_auto = was_auto;
+      apply(k, start, lg);
+      k->chunk_rows = start_rows;
       k->profiling = was_profiling;
     }
     return rc;
   };
-  // tile and work-item length with per-wavefront counting, then the block-aggregated
-  // counting at the best of those
+  // tile and work-item length (the untuned handle's among them) with per-wavefront counting,
+  // then the block-aggregated counting at the best of those
   float best = -1.0f;
   TuneChoice pick = start;
+  int rc = WPROJ_OK;
   for (int tile : kTuneTiles) {
     if (tile_shape(k, tile).lds_bytes + 256 > k->max_lds) continue;
-    for (int chunk : kTuneChunks) {
+    const TuneChoice by_rows{tile, kDefaultChunk, 0, !k->stable_bins};
+    apply(k, by_rows, lg);
+    BinWorkspace W;
+    const int untuned = call_shape(k, nvis, W, nullptr, Binning::kGrid).chunk;
+    auto consider = [&](const TuneChoice &c) {
       float ms = 0.0f;
-      const int rc = time_one({tile, chunk, 0}, ms);
-      if (rc != WPROJ_OK) return rc;
-      if (best < 0.0f || ms < best) {
+      const int rc = time_one(c, ms);
+      if (rc == WPROJ_OK && (best < 0.0f || ms < best)) {
         best = ms;
-        pick = {tile, chunk, 0};
+        pick = c;
       }
-    }
+      return rc;
+    };
+    if (untuned < kTuneChunks[0] && (rc = consider(by_rows)) != WPROJ_OK) return rc;
+    for (int chunk : kTuneChunks)
+      if ((rc = consider(chunk == untuned ? by_rows : TuneChoice{tile, chunk, 0, false})) != WPROJ_OK) return rc;
   }
   {
     float ms = 0.0f;
-    const int rc = time_one({pick.tile, pick.chunk, 1}, ms);
-    if (rc != WPROJ_OK) return rc;
-    if (ms < best) pick.bin_aggregate = 1;
+    TuneChoice aggregated = pick;
+    aggregated.bin_aggregate = 1;
+    if ((rc = time_one(aggregated, ms)) != WPROJ_OK) return rc;
+    if (ms < best) pick = aggregated;
   }
-  set(pick);
+  apply(k, pick, lg);
   k->profiling = was_profiling;
   std::lock_guard<std::mutex> lk(g_tune_mu);
   g_tune_cache[key] = pick;

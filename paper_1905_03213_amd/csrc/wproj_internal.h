@@ -221,7 +221,9 @@ struct wproj_kernels {
   bool plane_in_key = true; // bin by (tile, plane) rather than tile alone
   int chunk = 2048;         // max records per gridder work item
   int s_min = 0;            // smallest support
-  bool chunk_auto = false;  // nobody chose chunk: calls of few rows take shorter items
+  // calls of fewer rows than this take shorter items than chunk: all of them where nobody chose
+  // it, those of fewer rows than it was tuned for where the autotuner did
+  int64_t chunk_rows = 0;
   int bin_aggregate = 0;    // binning's count aggregation (wproj_params::bin_aggregate)
   int stable_bins = 0;      // records keep input order inside a bin (wproj_params::stable_bins)
   int n_cu = 256;           // compute units of the device
