@@ -87,17 +87,17 @@ __device__ inline uint32_t counter_of(const BinShape &B, uint32_t key, uint32_t 
   return (key << B.log2_rep) | (block & ((1u << B.log2_rep) - 1u));
 }
 
-// Where counter c of n lies when the counters are spread: column c mod 256 of rows of 256,
-// stored column by column.  Atomics on one cache line take turns (about 10 ns each), and
+// Where counter c of n lies when the counters are spread: column (c + skew floor(c / 256)) mod 256
+// of rows of 256, stored column by column.  Atomics on one cache line take turns (about 10 ns each), and
 // neighbouring tiles and a key's own counters are busy at the same time, so they are kept on
 // different lines: with 8 counters per key side by side the key pass gained nothing from
 // them (1024^2 image, 4e6 rows: binning 0.67 ms, spread 0.24).
-__device__ inline int64_t counter_place(uint32_t c, int64_t n) {
-  return (int64_t)(c & 255u) * counter_column(n) + (c >> 8);
+__device__ inline int64_t counter_place(uint32_t c, int64_t n, uint32_t skew) {
+  return (int64_t)((c + (c >> 8) * skew) & 255u) * counter_column(n) + (c >> 8);
 }
 __device__ inline uint32_t *counter_at(const BinShape &B, uint32_t *count, uint32_t key, uint32_t block) {
   const uint32_t c = counter_of(B, key, block);
-  return count + (B.spread ? counter_place(c, B.n_counts) : (int64_t)c);
+  return count + (B.spread ? counter_place(c, B.n_counts, B.skew) : (int64_t)c);
 }
 
 __device__ inline double wave_sum(double v) {
@@ -704,21 +704,21 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t *sh, uint32
 }
 
 template <bool SPREAD>
-__device__ inline void scan_load(const uint32_t *__restrict__ in, int64_t n, uint32_t (&v)[kScanItems]) {
+__device__ inline void scan_load(const uint32_t *__restrict__ in, int64_t n, uint32_t skew, uint32_t (&v)[kScanItems]) {
   const int64_t base = (int64_t)blockIdx.x * kScanTile;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const int64_t i = base + k * kScanBlock + threadIdx.x;
-    v[k] = i < n ? in[SPREAD ? counter_place((uint32_t)i, n) : i] : 0u;
+    v[k] = i < n ? in[SPREAD ? counter_place((uint32_t)i, n, skew) : i] : 0u;
   }
 }
 
 template <bool SPREAD>
 __global__ void __launch_bounds__(kScanBlock)
-    scan_sums_of_tiles_kernel(const uint32_t *__restrict__ in, int64_t n, uint32_t *__restrict__ tile_sums) {
+    scan_sums_of_tiles_kernel(const uint32_t *__restrict__ in, int64_t n, uint32_t skew, uint32_t *__restrict__ tile_sums) {
   __shared__ uint32_t sh[kScanBlock / 64];
   uint32_t v[kScanItems], s = 0, total;
-  scan_load<SPREAD>(in, n, v);
+  scan_load<SPREAD>(in, n, skew, v);
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) s += v[k];
   block_exclusive_scan(s, sh, total);
@@ -743,14 +743,14 @@ __global__ void __launch_bounds__(1024) scan_sums_kernel(uint32_t *sums, int64_t
 // (the block adds up those before its own), else their scan.
 template <bool SPREAD, bool SELF>
 __global__ void __launch_bounds__(kScanBlock)
-    scan_tiles_kernel(const uint32_t *__restrict__ in, uint32_t *__restrict__ out, int64_t n,
+    scan_tiles_kernel(const uint32_t *__restrict__ in, uint32_t *__restrict__ out, int64_t n, uint32_t skew,
                       const uint32_t *__restrict__ tile_sums) {
   __shared__ uint32_t sh[kScanBlock / 64];
   __shared__ uint32_t tile[kScanTile + kScanTile / kScanItems];
   auto at = [](int i) { return i + i / kScanItems; };  // padded against bank conflicts
   const int t = threadIdx.x;
   uint32_t v[kScanItems], total;
-  scan_load<SPREAD>(in, n, v);
+  scan_load<SPREAD>(in, n, skew, v);
   uint32_t before;
   if constexpr (SELF) {
     uint32_t mine = 0;
@@ -958,22 +958,23 @@ int64_t radix_digit_slots(int64_t nvis) {
 }
 
 template <bool SPREAD>
-static hipError_t exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {
+static hipError_t exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t skew, uint32_t *tmp,
+                                 hipStream_t s) {
   const int64_t tiles = (n + kScanTile - 1) / kScanTile;
   const dim3 grid((unsigned)tiles), block(kScanBlock);
-  if (tiles > 1) hipLaunchKernelGGL(scan_sums_of_tiles_kernel<SPREAD>, grid, block, 0, s, in, n, tmp);
+  if (tiles > 1) hipLaunchKernelGGL(scan_sums_of_tiles_kernel<SPREAD>, grid, block, 0, s, in, n, skew, tmp);
   if (tiles <= kScanSelf) {
-    hipLaunchKernelGGL((scan_tiles_kernel<SPREAD, true>), grid, block, 0, s, in, out, n, tmp);
+    hipLaunchKernelGGL((scan_tiles_kernel<SPREAD, true>), grid, block, 0, s, in, out, n, skew, tmp);
   } else {
     hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(1024), 0, s, tmp, tiles);
-    hipLaunchKernelGGL((scan_tiles_kernel<SPREAD, false>), grid, block, 0, s, in, out, n, tmp);
+    hipLaunchKernelGGL((scan_tiles_kernel<SPREAD, false>), grid, block, 0, s, in, out, n, skew, tmp);
   }
   return hipGetLastError();
 }
 
 // out[i] = sum_{k < i} in[i], out[n] = total (out has n + 1 entries).
 hipError_t launch_exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {
-  return exclusive_scan<false>(in, out, n, tmp, s);
+  return exclusive_scan<false>(in, out, n, 0u, tmp, s);
 }
 
 hipError_t launch_plan_rows(const wproj_kernels *k, const BinShape &B, const BinWorkspace &W, int64_t nvis,
@@ -1027,8 +1028,8 @@ hipError_t launch_bin(const wproj_kernels *k, const BinShape &B, int64_t nvis, c
       key_pass(float{}, std::false_type{});
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  e = B.spread ? exclusive_scan<true>(W.count, W.offset, B.n_counts, W.scan_tmp, s)
-               : exclusive_scan<false>(W.count, W.offset, B.n_counts, W.scan_tmp, s);
+  e = B.spread ? exclusive_scan<true>(W.count, W.offset, B.n_counts, B.skew, W.scan_tmp, s)
+               : exclusive_scan<false>(W.count, W.offset, B.n_counts, 0u, W.scan_tmp, s);
   if (e != hipSuccess) return e;
   if (k->params.precision == WPROJ_F64)
     e = tapword ? place_records<double, double2, RecordF64, true>(k, B, nvis, vis, wt, W, S_fix, zero_out, s)

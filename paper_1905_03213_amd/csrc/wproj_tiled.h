@@ -275,6 +275,7 @@ struct BinShape {
   int64_t n_tiles;   // n_images * ntx * nty
   int log2_rep;      // a key's visibilities are counted in 2^log2_rep counters, by the key pass's block
   int spread;        // neighbouring counters are stored on different cache lines (counter_place)
+  uint32_t skew;     // spread: columns a row of counters is shifted by from the row before
   int64_t n_keys;    // n_tiles * kw
   int64_t n_counts;  // n_keys << log2_rep
 };
