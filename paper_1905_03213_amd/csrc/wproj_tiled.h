@@ -183,7 +183,8 @@ __device__ inline double bcast(double v, int j) {
 // that uses a record's field broadcasts it by itself, with no v_readlane before it.
 // After the registers are replicated, dpp_ready covers the two wait states that a DPP read
 // needs after a vector write (the assembler statements below hide the DPP read from the
-// compiler's hazard handling).  DPP reads nothing from a lane that is switched
+// compiler's hazard handling; a CPU test looks for reads that come too early in the built
+// kernels).  DPP reads nothing from a lane that is switched
 // off, so these run with all 64 lanes on.
 template <int I> __device__ inline uint32_t row_bcast(uint32_t v) {
   static_assert(I >= 0 && I < 16, "a row has 16 lanes");
