@@ -534,7 +534,7 @@ __global__ void __launch_bounds__(64 * kMaxWavesPerBlock)
       load_rec(kBatch, nxt);
       Batch cur = unpack(now);
       Raw c0[kVarGroup], c1[kVarGroup];
-      fetch_group(std::integral_constant<int, 0>{}, cur, c0);
+      if (__ballot(cur.support > 8u) == 0) fetch_group(std::integral_constant<int, 0>{}, cur, c0);
       for (uint32_t b = 0; b < n_rec; b += kBatch) {
         load_vis(nxt, vnext);
         const bool one_pass = __ballot(cur.support > 8u) == 0;
