@@ -305,7 +305,7 @@ struct BinWorkspace {
   uint32_t *choff;     // [n_tiles + 1]; choff[n_tiles] = number of work items
   WorkItem *items;     // [max_items]
   uint32_t *scan_tmp;  // scan_temp_words of the scans, work_temp_words(n_tiles)
-  uint32_t *queues;    // [kQueues * kQueueStride] heads of the work queues, over wslots
+  uint32_t *queues;    // [kQueues * kQueueStride] heads of the work queues
   uint32_t *order;     // [max_items] work-item indices, largest items first
   uint32_t *order_cnt; // [2 * kOrderBuckets] per size class: item count, placement cursor
   int64_t nvis;        // rows of the call
