@@ -100,6 +100,9 @@ template <> struct TapRaw<double2> {  // the per-record-support fast path is FP3
   typedef double2 T;
 };
 constexpr int kMaxWavesPerBlock = 4;
+// Support parameter of the kernel for large supports, and the rows from which it is taken.
+constexpr int kLargeSupports = -1;
+constexpr int64_t kManyLargeRows = 1 << 21;
 
 // A row-carrying record (weight, row) turned into W V from the visibility it names; a
 // negative weight marks a Hermitian-folded row, which enters as W conj(V).
@@ -130,7 +133,7 @@ __device__ inline void mac_bcast(C2 &v, Real wr, Real wi, const Tap &t) {
   fmac_bcast<I>(v.y, wi, t.x);
 }
 
-// S = fixed support (0 = per-record support).  PLANNED: the records are row-carrying
+// S = fixed support (0 = per-record support, kLargeSupports = per-record support, light).  PLANNED: the records are row-carrying
 // (weight, row) and W V is formed from vis[row] as each record is loaded.  RUNS (paired
 // fixed-support path only): while consecutive records of the work item share the
 // footprint origin, each lane keeps its cell of the footprint in a register and writes it
@@ -412,7 +415,7 @@ __global__ void __launch_bounds__(64 * kMaxWavesPerBlock)
         });
         cur = next;
       }
-    } else if constexpr (kHasTap<Rec> && std::is_same_v<Real, float>) {
+    } else if constexpr (kHasTap<Rec> && std::is_same_v<Real, float> && S == 0) {
       // Per-record supports with FP32 arithmetic: lane t handles taps t, 64 + t, ... of a
       // record.  The lane's cells follow the support and are recomputed only when it changes (a
       // tile's records come plane by plane).  A batch whose supports all take one pass (S <= 8)
@@ -568,6 +571,30 @@ __global__ void __launch_bounds__(64 * kMaxWavesPerBlock)
         if (one_pass) add_group(std::integral_constant<int, 1>{}, cur, c1);
         cur = next;
       }
+    } else if constexpr (kHasTap<Rec> && S == kLargeSupports) {
+      // Large supports with FP32 arithmetic, taps loaded as they go: nothing held over records,
+      // so that registers leave room for every wavefront whose tile copy LDS holds.
+      Rec now, nxt, nxt2;
+      C2 vnext;
+      load_batch(0, now);
+      load_rec(kBatch, nxt);
+      for (uint32_t b = 0; b < n_rec; b += kBatch) {
+        load_vis(nxt, vnext);
+        load_rec(b + 2 * kBatch, nxt2);
+#pragma unroll 1
+        for (int j = 0; j < (int)min(kBatch, n_rec - b); ++j) {
+          const uint32_t tp = bcast(now.tap, j);
+          const int Sr = (int)(tp >> kTapBits) + 1, base = (int)(bcast(now.lds, j) & kLdsMask);
+          const Real rwr = bcast(now.wr, j), rwi = bcast(now.wi, j);
+          for (int t = lane; t < Sr * Sr; t += 64) {
+            const int kv = t / Sr, ku = t - kv * Sr;
+            accumulate(acc, base + kv * pitch + ku, rwr, rwi, tab_load(tab, (tp & kTapMask) + (uint32_t)t));
+          }
+        }
+        weigh(b + kBatch, nxt, vnext);
+        now = nxt;
+        nxt = nxt2;
+      }
     } else if constexpr (kHasTap<Rec>) {
       // General path (FP64; per-record support up to 32): records by wave-uniform loads,
       // each record's taps in passes of 64 lanes.
@@ -654,6 +681,16 @@ hipError_t dispatch_support(const wproj_kernels *k, const BinShape &B, const Til
     else
       return dispatch_fixed<Real, Rec, Tab, PLANNED, kMinFixedSupport>(k, B, ts, W, grid, vis, s);
   }
+  // Supports above 16 alone over many rows: the kernel for mixed supports holds 188 registers with an
+  // FP32 table (140 with FP16) and so 8 (12) wavefronts a CU, where LDS holds up to 16 copies of
+  // 16-cell tiles.  Gridder call, mixed kernel and light one, S = 17, 16-cell tiles: 8.1e6 rows on
+  // 2048^2 4.11 and 2.85 ms (FP16 2.61 and 2.31), on 4096^2 4.04 and 2.99, 4.0e6 on 2048^2 2.73 and
+  // 1.90; S = 24 9.01 and 7.04; 32-cell tiles alike (4.0e6 rows 3.57 and 3.52).  Fewer rows go
+  // either way (S = 17, 2.0e6 on 2048^2 1.25 and 1.25, with 8 planes 0.98 and 1.03; 1.0e6 on 512^2
+  // 0.73 and 0.61, but S = 20 1.02 and 1.16).
+  if constexpr (std::is_same_v<Real, float>)
+    if (k->s_min > 16 && W.nvis > kManyLargeRows)
+      return launch_one<Real, Rec, Tab, kLargeSupports, PLANNED>(k, B, ts, W, grid, vis, s);
   return launch_one<Real, Rec, Tab, 0, PLANNED>(k, B, ts, W, grid, vis, s);
 }
 
