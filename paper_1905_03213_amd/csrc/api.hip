@@ -229,13 +229,13 @@ inline int64_t align_up(int64_t x) { return (x + kAlign - 1) / kAlign * kAlign; 
 // while 2^18 hold them (1e7 rows on 16 layers of 2048^2, 65536 bins: 0.72 ms with 1, 0.51
 // with 4, 0.49 with 8; 64 images of 1024^2 with the aggregated key pass: 1.10, 1.13, 1.37),
 // and never more counters than the planes' bins would have needed, so the workspace does
-// not grow.  More than 16 a bin are for few tiles with many rows (call of 2.0e6 rows on 256^2
-// with 16 and up to 64: tiles of 16 265 and 223 us, of 32 700 and 230, of 64 1626 and 457; with
-// the planes 404, 535 and 1193); beyond one scan tile's 4096 counters they need 16 rows each (1.0e5
-// rows on 256^2, tiles of 16: 68 us with 4096, 69 to 71 with more; 5.1e5: 142 and 127).  Where the
-// planes allow fewer than 1024 counters, neighbouring planes' rows spread better over them than
-// the blocks do (8 planes, 1.0e5 to 2.0e6 rows, with planes over by tile: 512 counters 0.92 to
-// 0.98, 128 0.88 to 0.95; 2048 1.19 to 1.5).
+// not grow.  More than 16 a bin are for few tiles with many rows (call of 2.0e6 rows on
+// 256^2 with 16 and up to 64: tiles of 16 265 and 223 us, of 32 700 and 230, of 64 1626 and
+// 457; with the planes 404, 535 and 1193); beyond one scan tile's 4096 counters they need 16
+// rows each (1.0e5 rows on 256^2, tiles of 16: 68 us with 4096, 69 to 71 with more; 5.1e5: 142
+// and 127).  Where the planes allow fewer than 1024 counters, neighbouring planes' rows spread
+// better over them than the blocks do (8 planes, 1.0e5 to 2.0e6 rows, with planes over by tile:
+// 512 counters 0.92 to 0.98, 128 0.88 to 0.95; 2048 1.19 to 1.5).
 // Larger tables than this keep the planes: without their order the taps no longer come from the
 // 4 MB of an XCD's L2 (FP64 on 2048^2, 128 planes, call by tile and by plane: 18.9 MB of S = 12
 // 8.96 and 9.07 ms, 22.2 MB of S = 13 10.66 and 9.89, 33.6 MB of S = 16 17.1 and 15.0; FP32,
@@ -418,12 +418,12 @@ int64_t workspace_bytes_for(const wproj_kernels *k, int64_t nvis) {
 }
 
 // Work-item length of a call: the handle's, or, where neither the caller nor the autotuner
-// chose one for so few rows, down to kMinAutoChunk so that a call of few rows still gives each wavefront that
-// fits on the device an item (2e4 rows in FP64 on 256^2: gridder 99 us with items of 2048, of
-// which the busiest tile's runs alone, 25 with items of 128; 1024^2, 4e6 rows, support 9: 293
-// -> 188 us), as far
-// as the workspace that the autotuner's choices need holds the partial tiles.  With stable
-// bins the length stays as it is, since a reproducible grid's rounding follows it.
+// chose one for so few rows, down to kMinAutoChunk so that a call of few rows still gives each
+// wavefront that fits on the device an item (2e4 rows in FP64 on 256^2: gridder 99 us with items
+// of 2048, of which the busiest tile's runs alone, 25 with items of 128; 1024^2, 4e6 rows, support
+// 9: 293 -> 188 us), as far as the workspace that the autotuner's choices need holds the partial
+// tiles.  With stable bins the length stays as it is, since a reproducible grid's rounding follows
+// it.
 // With a fixed support a CU's share is split between the wavefronts whose tile copies LDS holds:
 // of large copies few fit, and each costs more (FP64, S = 16, 16-cell tiles, 4e6 rows: 1.34 ms
 // with items of 512, 1.22 with 2048; S = 8: 0.484 with 512, 0.474 with 1024).  Elsewhere 32

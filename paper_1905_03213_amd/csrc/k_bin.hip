@@ -232,7 +232,7 @@ __global__ void __launch_bounds__(kBinBlock)
   }
   // Counters and weight sums: reduced over the workgroup in LDS, then one atomic per
   // workgroup into one of kSlots partial accumulators (chosen by block index) so that
-  // no address is hit by many workgroups; finalize_kernel adds the slots up.
+  // no address is hit by many workgroups; finalize_wave adds the slots up.
   __shared__ double s_w[kBinBlock / 64];
   __shared__ unsigned s_c[3][kBinBlock / 64];
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;

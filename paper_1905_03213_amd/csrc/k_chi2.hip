@@ -4,8 +4,8 @@
 //   chi2 = sum_j w_j |o_j - p_j|^2,   g_j = d chi2 / d Re p_j + i d chi2 / d Im p_j
 //        = -2 w_j (o_j - p_j).
 // The sum is taken in FP64 in a fixed order (each thread of a fixed grid strides through
-// the visibilities, blocks reduce in LDS, one block adds the block sums in index order),
-// so its value does not depend on scheduling.
+// the visibilities and blocks reduce in LDS; one block's threads then stride through the
+// block sums and reduce in the same tree), so its value does not depend on scheduling.
 #include <algorithm>
 
 #include "wproj_internal.h"

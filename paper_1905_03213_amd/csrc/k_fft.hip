@@ -5,8 +5,9 @@
 //
 // Bound by HBM: each pass reads and writes the data once, where rocFFT's passes and those of
 // the Hermitian part and the correction around them are five or more.  Transform and
-// correction together, rocFFT's way and here: 64 FP32 images of 1024^2 745 and 277 us (1.6 GB
-// in two passes at 5.8 TB/s); one of 2048^2 74 and 33 us in FP32, 96 and 47 us in FP64; FP64
+// correction together, rocFFT's way and here: 64 FP32 images of 1024^2 745 and 277 us (1.34 GB
+// in two passes, 4.9 TB/s; the column pass asks for the half spectrum E twice, the second time
+// served by the caches); one of 2048^2 74 and 33 us in FP32, 96 and 47 us in FP64; FP64
 // image -> grid of 2048^2 120 and 50 us; FP32 4096^2 201 and 111 us; FP64 256^2 23 and 15 us;
 // 16 FP32 w-stacking layers of 2048^2 984 and 384 us.
 //

@@ -6,11 +6,11 @@
 namespace wproj {
 namespace {
 
-// Adds the partial tiles to the grid.  One thread per grid cell (each thread takes two
-// cells of a column) sums, in FP64, every work item's partial value for that cell: the items of the cell's own tile and those of
-// the tiles to its left/above whose halo reaches it (items of tile t are contiguous in
-// the work list: [choff[t], choff[t + 1])).  Each cell has exactly one writer, so the
-// grid update needs no atomics and the result does not depend on scheduling.
+// Adds the partial tiles to the grid.  A thread takes two cells of a column and sums, in
+// FP64, every work item's partial value for each of them: the items of the cell's own tile
+// and those of the tiles to its left/above whose halo reaches it (items of tile t are
+// contiguous in the work list: [choff[t], choff[t + 1])).  Each cell has exactly one writer,
+// so the grid update needs no atomics and the result does not depend on scheduling.
 constexpr int kReduceAhead = 6;
 
 template <typename Real>
