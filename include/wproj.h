@@ -100,8 +100,9 @@ typedef struct {
   int32_t n_images;         /* >= 1: independent images gridded in one call (e.g. channels) */
   int32_t algorithm;        /* wproj_algorithm */
   int32_t tile;             /* tiled gridder tile side: 0 = default (16), else 16, 32 or 64 */
-  int32_t chunk;            /* tiled gridder work-item length in records: 0 = default (2048, less
-                               in calls of few rows without stable_bins), else 256..65536 */
+  int32_t chunk;            /* tiled gridder work-item length in records: 0 = default (2048; less in
+                               calls of few rows and, with supports above 8, in degridding, both
+                               without stable_bins), else 256..65536 */
   int32_t w_mode;           /* wproj_w_mode (0 = linear planes over [-w_max, w_max]).  The fold
                                halves the planes (and tables) needed for a given plane spacing:
                                with a real sky V(-u,-v,-w) = conj(V(u,v,w)), so Re of the image
@@ -293,10 +294,11 @@ int wproj_check_weights(const wproj_kernels *k, const double *weight_sum, void *
  * Choose the tiled gridder's tile side (16, 32 or 64 cells, each where one wavefront's
  * tile copy with its halo fits in a workgroup's LDS) and work-item length (1024 ..
  * 16384 binned records, or, without stable_bins, the untuned handle's length) for this
- * handle by timing each candidate on the caller's data (one warm-up and one timed wproj_grid per candidate, HIP events on `stream`), then, at
- * the fastest of those, binning with counts aggregated per block (bin_aggregate = 1)
- * against per-wavefront runs (0), and keep the fastest configuration in the handle.  The choice is also cached per problem shape (grid size,
- * images, planes, supports, oversampling, precision, visibility count rounded to a
+ * handle by timing each candidate on the caller's data (one warm-up and one timed wproj_grid
+ * per candidate, HIP events on `stream`), then, at the fastest of those, binning with counts
+ * aggregated per block (bin_aggregate = 1) against per-wavefront runs (0), and keep the
+ * fastest configuration in the handle.  The choice is also cached per problem shape (grid
+ * size, images, planes, supports, oversampling, precision, visibility count rounded to a
  * power of two) for the life of the process, and later calls on a handle of the same
  * shape reuse it without timing.  Arguments are those of wproj_grid; scratch_grid
  * ([n_images][n][n], device) is written with garbage.  Synchronises `stream`.  Mutates
@@ -304,8 +306,8 @@ int wproj_check_weights(const wproj_kernels *k, const double *weight_sum, void *
  * flattening of its scaling curves to workload imbalance between threads and nodes
  * (Sections 3.2, 4); the work-item length is the knob that trades that imbalance
  * against per-item overhead (work items are handed out largest first, so the imbalance
- * left is mostly that of the last, smallest items).  Errors: as wproj_grid; WPROJ_EUNSUPPORTED for a handle
- * built with WPROJ_ALGO_PLAIN.
+ * left is mostly that of the last, smallest items).  Errors: as wproj_grid;
+ * WPROJ_EUNSUPPORTED for a handle built with WPROJ_ALGO_PLAIN.
  */
 int wproj_autotune(wproj_kernels *k, int64_t nvis, const double *uvw, const void *vis,
                    const void *weight, const int64_t *image_offsets, void *scratch_grid,
@@ -313,7 +315,7 @@ int wproj_autotune(wproj_kernels *k, int64_t nvis, const double *uvw, const void
 
 /* The tiled gridder configuration in use: *tile (cells), *chunk (records; without
  * stable_bins the most a work item holds: calls of few rows, or of fewer rows than the
- * handle was tuned for, take shorter items) and *bin_aggregate
+ * handle was tuned for, and degridding with supports above 8 take shorter items) and *bin_aggregate
  * (wproj_params::bin_aggregate); host pointers, each nullable. */
 int wproj_tuning(const wproj_kernels *k, int32_t *tile, int32_t *chunk, int32_t *bin_aggregate);
 

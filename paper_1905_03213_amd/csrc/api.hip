@@ -250,11 +250,16 @@ constexpr int64_t kMaxTileBinTable = 20000000;
 // planes, FP32 S = 12 (9.4 MB) 0.93, S = 14 (12.8 MB) 0.92, FP64 S = 11 (15.9 MB) 0.93; 24 planes
 // (under 4 MB) 1.02 to 1.4.  T = 16: FP32 S = 16 of 96 planes (12.6 MB) 0.94 to 1.01, of 128 (16.8
 // MB) 0.96, FP64 S = 12 of 96 (14.2 MB) 0.97 to 1.03, S = 14 of 64 (12.8 MB) 1.00 to 1.03, FP32
-// S = 14 of 64 (7.3 MB) 1.00 to 1.04.  Many images, whose rows come with one channel each and so
-// without runs that tile bins would join, keep the planes for tiles of 32 in any case (32 planes,
-// S = 9 and 13: 64 images of 512^2 0.90 and 0.91, 256 of 256^2 0.85 and 0.89, 64 of 1024^2 0.99
-// and 0.97, but 4 of 1024^2 1.20 and 1.05; T = 16 0.98 to 1.04).
+// S = 14 of 64 (7.3 MB) 1.00 to 1.04.  Many images, whose rows come with one
+// channel each and so without runs that tile bins would join, keep the planes for tiles of 32 in
+// any case (32 planes, S = 9 and 13: 64 images of 512^2 0.90 and 0.91, 256 of 256^2 0.85 and 0.89,
+// 64 of 1024^2 0.99 and 0.97, but 4 of 1024^2 1.20 and 1.05; T = 16 0.98 to 1.04).
 constexpr int64_t kMaxTileBinTableRows[2] = {12500000, 9000000};  // tiles of 16, of 32 and more
+constexpr int64_t kManyDegridRows = 1 << 19;
+constexpr int64_t kCuLds = 160 * 1024;
+// A CU holds one tile copy only (FP64 tiles of 64): its eight wavefronts need long items (3.9e6 rows
+// on 512^2 and 1024^2, S = 10 of 60 planes, items of 256 over 2048 1.09 and 1.11).
+bool one_copy(const wproj_kernels *k, int tile) { return 2 * (int64_t)tile_shape(k, tile).lds_bytes > kCuLds; }
 constexpr int kManyImages = 16;
 constexpr int kMaxLog2Rep = 8, kLog2RepAnyRows = 4;
 constexpr int64_t kFewCounters = 1 << 10, kScanTileCounters = 1 << 12, kRowsPerCounter = 16;
@@ -299,8 +304,10 @@ BinShape bin_shape(const wproj_kernels *k, int64_t once_rows = -1, bool degrid =
   const int64_t table_bytes = n_sub * k->s_max * k->s_max *
                               (k->params.precision == WPROJ_F64 ? 16 : k->params.precision == WPROJ_F32 ? 8 : 4);
   int64_t most_bytes = kMaxTileBinTable;
-  if (degrid && k->s_max > 8)
-    most_bytes = B.tile >= 32 && k->params.n_images >= kManyImages ? 0 : kMaxTileBinTableRows[B.tile >= 32];
+  if (degrid && k->s_max > 8) {
+    most_bytes = kMaxTileBinTableRows[B.tile >= 32];
+    if (B.tile >= 32 && k->params.n_images >= kManyImages) most_bytes = 0;
+  }
   if (once_rows >= 0 && B.pack_sub && !B.stable && table_bytes <= most_bytes) {
     const int64_t room = B.n_keys;
     const int64_t best = once_rows > kManyRows ? kBestCountersManyRows : kBestCounters;
@@ -329,8 +336,9 @@ int64_t max_keys(const wproj_kernels *) { return (int64_t)0x7fffffffll; }
 
 // Lays the binning buffers out from `base` (nullptr: sizes only); returns total bytes.
 // B: the shape with the planes in the key where they may be (bin_shape without once_rows), which
-// needs the most room.
-int64_t carve(const wproj_kernels *k, const BinShape &B, int64_t nvis, char *base, BinWorkspace &W) {
+// needs the most room.  partials: with the items' partial tiles, which degridding alone lacks.
+int64_t carve(const wproj_kernels *k, const BinShape &B, int64_t nvis, char *base, BinWorkspace &W,
+              bool partials = true) {
   const int64_t rec_bytes = k->params.precision == WPROJ_F64 ? sizeof(RecordF64) : sizeof(RecordF32);
   // a tile with r records gives ceil(r / chunk) <= r / chunk + 1 items, and at most
   // min(n_tiles, nvis) tiles hold records
@@ -370,7 +378,7 @@ int64_t carve(const wproj_kernels *k, const BinShape &B, int64_t nvis, char *bas
   W.max_items = max_items;
   const TileShape ts = tile_shape(k, B.tile);
   const int64_t cplx = k->params.precision == WPROJ_F64 ? 16 : 8;
-  W.partial = take(max_items * (int64_t)ts.rows * ts.rows * cplx);
+  W.partial = partials ? take(max_items * (int64_t)ts.rows * ts.rows * cplx) : nullptr;
   for (int i = 0; i < 2; ++i) {
     W.sort_keys[i] = B.stable ? (uint32_t *)take(4 * nvis) : nullptr;
     W.sort_vals[i] = B.stable ? (uint32_t *)take(4 * nvis) : nullptr;
@@ -434,25 +442,38 @@ int64_t workspace_bytes_for(const wproj_kernels *k, int64_t nvis) {
 // wavefronts' batches: its records take so little time that the copies of a tile for a few of
 // them each are what counts.  Call with the gridder's length and with this, support 8, 64 planes,
 // 16-cell tiles: 1.0e5 rows on 256^2 47 and 42 us, 5.1e5 102 and 82, 2.0e6 198 and 179, on 1024^2
-// 191 and 171, on 2048^2 243 and 232; 2.0e4 rows and, on 1024^2, 1.0e5 the same.  With larger
-// supports and in FP64 no length from 256 to 2048 is more than 5 % faster than the gridder's for
-// 5.1e5 and 2.0e6 rows.
-constexpr int kMinAutoChunk = 128, kMinDegridChunk = 512;
-constexpr int64_t kCuLds = 160 * 1024;
+// 191 and 171, on 2048^2 243 and 232; 2.0e4 rows and, on 1024^2, 1.0e5 the same.
+// With larger supports, all alike, its records take longer, and short items keep the rows whose
+// taps are alike next to each other in time: at most 256 records, whatever the autotuner chose for
+// the gridder, unless tiles hold so few that copying them is what counts (a call with 256 over one
+// with the gridder's length, 40 planes, 3.9e6 rows on 1024^2: FP32 S = 9 0.95 with 16-cell tiles and
+// 0.83 with 32, S = 16 0.94 and 0.94, S = 24 0.96 and 0.98, FP64 S = 13 0.93 and 0.92, FP16 S = 14
+// 0.88 and 0.85; 8.0e5 rows on 256^2, 32-cell tiles, FP64 S = 13 0.81; 512 halves the gain; 49 rows
+// a 16-cell tile, 8.0e5 on 2048^2, 1.05 to 1.10).  With fewer rows only records of many tap bytes
+// gain, where few workgroups have anything to do (4.0e5 rows, 32-cell tiles: FP32 S = 9 to 11 and
+// FP16 1.05 to 1.13 on 256^2 to 1024^2; on 256^2 FP32 S = 16 0.88 to 0.92, FP64 S = 13 0.9).
+// Degridding needs no partial tiles.
+constexpr int kMinAutoChunk = 128, kMinDegridChunk = 512, kDegridChunk = 256;
+constexpr int64_t kDegridChunkTileRows = 128, kDegridChunkTapBytes = 1280;
 enum class Binning { kGrid, kDegrid, kPlan };  // of a single call, or kept
 BinShape call_shape(const wproj_kernels *k, int64_t nvis, BinWorkspace &W, char *base, Binning what) {
   BinShape full = bin_shape(k);
-  if (nvis < k->chunk_rows) {
+  const bool short_items =
+      what == Binning::kDegrid && ((full.pack_sub && k->s_max > 8) || k->s_min > kMaxFixedSupport) &&
+      !one_copy(k, k->tile) && nvis >= kDegridChunkTileRows * full.n_tiles &&
+      (nvis >= kManyDegridRows || (int64_t)k->s_max * k->s_max * (int64_t)k->tap_bytes >= kDegridChunkTapBytes);
+  if (nvis < k->chunk_rows || (short_items && k->chunk_rows > 0)) {
     const int64_t held = std::max<int64_t>(1, kCuLds / (int64_t)tile_shape(k, k->tile).lds_bytes);
     const int64_t waves = full.pack_sub ? std::min<int64_t>(32, held) : 32;
     const bool light = full.pack_sub && k->s_max <= 8 && k->params.precision != WPROJ_F64;
-    const int64_t want = what == Binning::kDegrid && light ? std::max<int64_t>(kMinDegridChunk, nvis / (2 * k->n_cu))
-                                                           : nvis / (k->n_cu * waves);
+    int64_t want = nvis / (k->n_cu * waves);
+    if (what == Binning::kDegrid && light) want = std::max<int64_t>(kMinDegridChunk, nvis / (2 * k->n_cu));
+    if (short_items) want = std::min<int64_t>(kDegridChunk, want);
     const int64_t limit = workspace_bytes_for(k, nvis);
     for (full.chunk = kMinAutoChunk; full.chunk < k->chunk; full.chunk *= 2)
-      if (full.chunk >= want && carve(k, full, nvis, nullptr, W) <= limit) break;
+      if (full.chunk >= want && carve(k, full, nvis, nullptr, W, !short_items) <= limit) break;
   }
-  carve(k, full, nvis, base, W);
+  carve(k, full, nvis, base, W, !short_items);
   if (what == Binning::kPlan) return full;
   BinShape B = bin_shape(k, nvis, what == Binning::kDegrid);
   B.chunk = full.chunk;
