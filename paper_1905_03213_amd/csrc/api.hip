@@ -250,15 +250,21 @@ constexpr int64_t kMaxTileBinTable = 20000000;
 // planes, FP32 S = 12 (9.4 MB) 0.93, S = 14 (12.8 MB) 0.92, FP64 S = 11 (15.9 MB) 0.93; 24 planes
 // (under 4 MB) 1.02 to 1.4.  T = 16: FP32 S = 16 of 96 planes (12.6 MB) 0.94 to 1.01, of 128 (16.8
 // MB) 0.96, FP64 S = 12 of 96 (14.2 MB) 0.97 to 1.03, S = 14 of 64 (12.8 MB) 1.00 to 1.03, FP32
-// S = 14 of 64 (7.3 MB) 1.00 to 1.04.  Many images, whose rows come with one
+// S = 14 of 64 (7.3 MB) 1.00 to 1.04.  With more rows and without FP64's dearer arithmetic the
+// taps are more of the call (8.0e5 to 1.0e7 rows on 256^2 to 2048^2, items of 256: 16 channels,
+// FP16 S = 14 of 118 planes (5.9 MB) 0.82 to 1.00, FP32 S = 16 of 48 (6.3 MB) and S = 12 of 118
+// (8.7 MB) 0.86 to 1.00, but S = 9 of 118 (4.9 MB) 0.87 to 1.05, FP16 S = 10 of 118 (3.0 MB) 0.96 to
+// 1.13; one channel 0.93 to 1.12, and 0.98 to 1.54).  Many images, whose rows come with one
 // channel each and so without runs that tile bins would join, keep the planes for tiles of 32 in
 // any case (32 planes, S = 9 and 13: 64 images of 512^2 0.90 and 0.91, 256 of 256^2 0.85 and 0.89,
 // 64 of 1024^2 0.99 and 0.97, but 4 of 1024^2 1.20 and 1.05; T = 16 0.98 to 1.04).
 constexpr int64_t kMaxTileBinTableRows[2] = {12500000, 9000000};  // tiles of 16, of 32 and more
-constexpr int64_t kManyDegridRows = 1 << 19;
+constexpr int64_t kMaxTileBinTableManyRows = 5000000, kManyDegridRows = 1 << 19;
 constexpr int64_t kCuLds = 160 * 1024;
-// A CU holds one tile copy only (FP64 tiles of 64): its eight wavefronts need long items (3.9e6 rows
-// on 512^2 and 1024^2, S = 10 of 60 planes, items of 256 over 2048 1.09 and 1.11).
+// A CU holds one tile copy only (FP64 tiles of 64): its eight wavefronts need long items, and with
+// larger tables the planes' order (3.9e6 rows on 512^2 and 1024^2, S = 10 of 60 planes (6.1 MB), call
+// by tile over call with the planes 1.04 and 1.12, with items of 256 1.14 and 1.25; S = 9 of 20 (1.7
+// MB), items of 2048, 0.84 and 0.78, S = 12 0.93 and 0.85).
 bool one_copy(const wproj_kernels *k, int tile) { return 2 * (int64_t)tile_shape(k, tile).lds_bytes > kCuLds; }
 constexpr int kManyImages = 16;
 constexpr int kMaxLog2Rep = 8, kLog2RepAnyRows = 4;
@@ -306,6 +312,8 @@ BinShape bin_shape(const wproj_kernels *k, int64_t once_rows = -1, bool degrid =
   int64_t most_bytes = kMaxTileBinTable;
   if (degrid && k->s_max > 8) {
     most_bytes = kMaxTileBinTableRows[B.tile >= 32];
+    if (once_rows >= kManyDegridRows && (k->params.precision != WPROJ_F64 || one_copy(k, B.tile)))
+      most_bytes = kMaxTileBinTableManyRows;
     if (B.tile >= 32 && k->params.n_images >= kManyImages) most_bytes = 0;
   }
   if (once_rows >= 0 && B.pack_sub && !B.stable && table_bytes <= most_bytes) {

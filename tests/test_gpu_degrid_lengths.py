@@ -1,6 +1,6 @@
-"""Single degridding calls with supports above 8, on both sides of the rule for short work items
-(rows per tile), untuned and tuned, with exactly the workspace that the library asks for, against
-the FP64 oracle."""
+"""Single degridding calls with supports above 8, on both sides of the rules for short work items
+(rows per tile) and for bins that keep the planes (rows, table size, copies a CU holds), untuned and tuned,
+with exactly the workspace that the library asks for, against the FP64 oracle."""
 
 import numpy as np
 import pytest
@@ -52,6 +52,16 @@ def _check(params, nvis, tuned=False):
 @pytest.mark.parametrize("prec,S", [("f32", 9), ("f64", 16), ("f32_f16table", 10), ("f32", 17)])
 def test_short_items(prec, S, nvis, tile):
     _check(dict(n=96, cell_rad=0.02 / 96, n_wplanes=3, w_max=80.0, support=S, oversample=8, kernel_image_size=32,
+                precision=prec, n_images=1, algorithm="tiled", tile=tile), nvis)
+
+
+# 2^19 rows; 5 MB of taps (FP32 S = 12: 73.7 kB a plane); one copy a CU (FP64 tiles of 64)
+@pytest.mark.parametrize("nvis,planes,prec,S,tile", [
+    (524287, 68, "f32", 12, 16), (524288, 68, "f32", 12, 16), (524288, 67, "f32", 12, 16), (524288, 68, "f64", 12, 16),
+    (524287, 20, "f64", 9, 64), (524288, 20, "f64", 9, 64), (524288, 20, "f32", 9, 64),
+])
+def test_planes_kept(nvis, planes, prec, S, tile):
+    _check(dict(n=96, cell_rad=0.02 / 96, n_wplanes=planes, w_max=80.0, support=S, oversample=8, kernel_image_size=32,
                 precision=prec, n_images=1, algorithm="tiled", tile=tile), nvis)
 
 
