@@ -242,7 +242,8 @@ inline int64_t align_up(int64_t x) { return (x + kAlign - 1) / kAlign * kAlign; 
 // 16.8 MB of S = 16, 6.92 and 7.06).
 constexpr int64_t kMaxTileBinTable = 20000000;
 // The row-per-lane degridder with supports above 8 gains less from the shorter binning and loses
-// more, since the wavefronts of an item then share no plane's taps: its limit is lower, and
+// more, since the wavefronts of an item then share no plane's taps: where its calls bin by tile at
+// all (call_shape), its limit is lower, and
 // lower still for tiles of 32 cells and more, of which a CU holds fewer copies.  A degridding
 // call's time with planes over its time by tile, 2.5e5 to 1.6e7 rows on 1024^2 to 4096^2.  T = 32:
 // 96 planes, FP32 S = 16 (12.6 MB) 0.92 to 0.98, FP64 S = 12 (14.2 MB) 0.95 to 0.99, FP32 S = 12
@@ -250,23 +251,19 @@ constexpr int64_t kMaxTileBinTable = 20000000;
 // planes, FP32 S = 12 (9.4 MB) 0.93, S = 14 (12.8 MB) 0.92, FP64 S = 11 (15.9 MB) 0.93; 24 planes
 // (under 4 MB) 1.02 to 1.4.  T = 16: FP32 S = 16 of 96 planes (12.6 MB) 0.94 to 1.01, of 128 (16.8
 // MB) 0.96, FP64 S = 12 of 96 (14.2 MB) 0.97 to 1.03, S = 14 of 64 (12.8 MB) 1.00 to 1.03, FP32
-// S = 14 of 64 (7.3 MB) 1.00 to 1.04.  With more rows and without FP64's dearer arithmetic the
-// taps are more of the call (8.0e5 to 1.0e7 rows on 256^2 to 2048^2, items of 256: 16 channels,
-// FP16 S = 14 of 118 planes (5.9 MB) 0.82 to 1.00, FP32 S = 16 of 48 (6.3 MB) and S = 12 of 118
-// (8.7 MB) 0.86 to 1.00, but S = 9 of 118 (4.9 MB) 0.87 to 1.05, FP16 S = 10 of 118 (3.0 MB) 0.96 to
-// 1.13; one channel 0.93 to 1.12, and 0.98 to 1.54).  Many images, whose rows come with one
-// channel each and so without runs that tile bins would join, keep the planes for tiles of 32 in
-// any case (32 planes, S = 9 and 13: 64 images of 512^2 0.90 and 0.91, 256 of 256^2 0.85 and 0.89,
-// 64 of 1024^2 0.99 and 0.97, but 4 of 1024^2 1.20 and 1.05; T = 16 0.98 to 1.04).
+// S = 14 of 64 (7.3 MB) 1.00 to 1.04.  Many images, whose rows come with one channel each and so
+// without runs that tile bins would join, keep the planes for tiles of 32 in any case (32 planes,
+// S = 9 and 13: 64 images of 512^2 0.90 and 0.91, 256 of 256^2 0.85 and 0.89, 64 of 1024^2 0.99
+// and 0.97, but 4 of 1024^2 1.20 and 1.05; T = 16 0.98 to 1.04).  Tiles of which a CU holds one copy
+// (FP64 tiles of 64) have the lowest limit (5.0e5 and 4.0e6 rows on 1024^2: S = 10 of 60 planes (6.1
+// MB) 0.90 and 0.89, S = 12 (8.8 MB) 0.89 and 0.88, S = 9 (5.0 MB) 1.09 and 1.09, of 20 1.18 and 1.27).
 constexpr int64_t kMaxTileBinTableRows[2] = {12500000, 9000000};  // tiles of 16, of 32 and more
-constexpr int64_t kMaxTileBinTableManyRows = 5000000, kManyDegridRows = 1 << 19;
-constexpr int64_t kCuLds = 160 * 1024;
-// A CU holds one tile copy only (FP64 tiles of 64): its eight wavefronts need long items, and with
-// larger tables the planes' order (3.9e6 rows on 512^2 and 1024^2, S = 10 of 60 planes (6.1 MB), call
-// by tile over call with the planes 1.04 and 1.12, with items of 256 1.14 and 1.25; S = 9 of 20 (1.7
-// MB), items of 2048, 0.84 and 0.78, S = 12 0.93 and 0.85).
-bool one_copy(const wproj_kernels *k, int tile) { return 2 * (int64_t)tile_shape(k, tile).lds_bytes > kCuLds; }
+constexpr int64_t kMaxTileBinTableOneCopy = 5500000;
 constexpr int kManyImages = 16;
+constexpr int64_t kCuLds = 160 * 1024;
+int64_t copies_held(const wproj_kernels *k, int tile) {
+  return std::max<int64_t>(1, kCuLds / (int64_t)tile_shape(k, tile).lds_bytes);
+}
 constexpr int kMaxLog2Rep = 8, kLog2RepAnyRows = 4;
 constexpr int64_t kFewCounters = 1 << 10, kScanTileCounters = 1 << 12, kRowsPerCounter = 16;
 constexpr int64_t kManyRows = 1ll << 25;
@@ -285,6 +282,12 @@ constexpr int64_t kMaxSpread = 1ll << 18;
 // 262 and 296), and so do, mostly, fewer than 4096 (2048, 256^2: 710, 730 and 866).
 constexpr uint32_t kSkew = 101;
 constexpr int64_t kMinSkewed = 1 << 12;
+
+void set_counters(BinShape &B) {
+  B.n_counts = B.n_keys << B.log2_rep;
+  B.spread = B.n_counts <= kMaxSpread;
+  B.skew = B.spread && B.log2_rep == 0 && B.n_counts >= kMinSkewed ? kSkew : 0u;
+}
 
 // once_rows: rows of a single call, -1 for a kept or stable binning.
 BinShape bin_shape(const wproj_kernels *k, int64_t once_rows = -1, bool degrid = false) {
@@ -312,8 +315,7 @@ BinShape bin_shape(const wproj_kernels *k, int64_t once_rows = -1, bool degrid =
   int64_t most_bytes = kMaxTileBinTable;
   if (degrid && k->s_max > 8) {
     most_bytes = kMaxTileBinTableRows[B.tile >= 32];
-    if (once_rows >= kManyDegridRows && (k->params.precision != WPROJ_F64 || one_copy(k, B.tile)))
-      most_bytes = kMaxTileBinTableManyRows;
+    if (copies_held(k, B.tile) == 1) most_bytes = kMaxTileBinTableOneCopy;
     if (B.tile >= 32 && k->params.n_images >= kManyImages) most_bytes = 0;
   }
   if (once_rows >= 0 && B.pack_sub && !B.stable && table_bytes <= most_bytes) {
@@ -332,9 +334,7 @@ BinShape bin_shape(const wproj_kernels *k, int64_t once_rows = -1, bool degrid =
       B.log2_rep = rep;
     }
   }
-  B.n_counts = B.n_keys << B.log2_rep;
-  B.spread = B.n_counts <= kMaxSpread;
-  B.skew = B.spread && B.log2_rep == 0 && B.n_counts >= kMinSkewed ? kSkew : 0u;
+  set_counters(B);
   return B;
 }
 
@@ -459,31 +459,46 @@ int64_t workspace_bytes_for(const wproj_kernels *k, int64_t nvis) {
 // 0.88 and 0.85; 8.0e5 rows on 256^2, 32-cell tiles, FP64 S = 13 0.81; 512 halves the gain; 49 rows
 // a 16-cell tile, 8.0e5 on 2048^2, 1.05 to 1.10).  With fewer rows only records of many tap bytes
 // gain, where few workgroups have anything to do (4.0e5 rows, 32-cell tiles: FP32 S = 9 to 11 and
-// FP16 1.05 to 1.13 on 256^2 to 1024^2; on 256^2 FP32 S = 16 0.88 to 0.92, FP64 S = 13 0.9).
+// FP16 1.05 to 1.13 on 256^2 to 1024^2; on 256^2 FP32 S = 16 0.88 to 0.92, FP64 S = 13 0.9).  Not
+// where a CU holds one tile copy only (FP64 tiles of 64; 3.9e6 rows, S = 10 1.09 to 1.11).
 // Degridding needs no partial tiles.
+// Such calls keep the planes, several counters a bin where there are few (the counters have the
+// partial tiles' room): tracks of 8 hours bring many planes into a tile, whose taps the records of a
+// short item share only when sorted by plane.  60 calls of 3.0e5 to 1.1e7 rows, S = 9 to 12, with
+// planes over by tile 0.96 on average, 0.85 to 1.07 (FP16 S = 10, 113 planes, 9.1e6 rows of 39
+// channels on 650^2 0.90); with one counter a bin 1.25 where planes are few (FP32 S = 9, 38 planes,
+// 1.0e6 rows of one channel on 342^2).  Where w follows v through all of the observation a tile holds
+// few planes and would gain (1024^2, 24 planes, 2.5e6 rows of one channel 1.2, of 16 channels 1.04).
 constexpr int kMinAutoChunk = 128, kMinDegridChunk = 512, kDegridChunk = 256;
-constexpr int64_t kDegridChunkTileRows = 128, kDegridChunkTapBytes = 1280;
+constexpr int64_t kDegridChunkTileRows = 128, kDegridChunkTapBytes = 1280, kManyDegridRows = 1 << 19;
 enum class Binning { kGrid, kDegrid, kPlan };  // of a single call, or kept
 BinShape call_shape(const wproj_kernels *k, int64_t nvis, BinWorkspace &W, char *base, Binning what) {
   BinShape full = bin_shape(k);
+  const int64_t held = copies_held(k, k->tile);
   const bool short_items =
-      what == Binning::kDegrid && ((full.pack_sub && k->s_max > 8) || k->s_min > kMaxFixedSupport) &&
-      !one_copy(k, k->tile) && nvis >= kDegridChunkTileRows * full.n_tiles &&
+      what == Binning::kDegrid && k->chunk_rows > 0 && held > 1 &&
+      ((full.pack_sub && k->s_max > 8) || k->s_min > kMaxFixedSupport) && nvis >= kDegridChunkTileRows * full.n_tiles &&
       (nvis >= kManyDegridRows || (int64_t)k->s_max * k->s_max * (int64_t)k->tap_bytes >= kDegridChunkTapBytes);
-  if (nvis < k->chunk_rows || (short_items && k->chunk_rows > 0)) {
-    const int64_t held = std::max<int64_t>(1, kCuLds / (int64_t)tile_shape(k, k->tile).lds_bytes);
+  BinShape B = full;
+  if (short_items && full.kw > 1) {
+    int &rep = B.log2_rep;
+    while (rep < kMaxLog2Rep && B.n_keys << (rep + 1) <= std::min(kBestCounters, nvis / kRowsPerCounter)) ++rep;
+    set_counters(B);
+    full.n_counts = B.n_counts;
+  } else if (what != Binning::kPlan) {
+    B = bin_shape(k, nvis, what == Binning::kDegrid);
+  }
+  if (nvis < k->chunk_rows || short_items) {
     const int64_t waves = full.pack_sub ? std::min<int64_t>(32, held) : 32;
     const bool light = full.pack_sub && k->s_max <= 8 && k->params.precision != WPROJ_F64;
     int64_t want = nvis / (k->n_cu * waves);
     if (what == Binning::kDegrid && light) want = std::max<int64_t>(kMinDegridChunk, nvis / (2 * k->n_cu));
-    if (short_items) want = std::min<int64_t>(kDegridChunk, want);
+    if (short_items) want = kDegridChunk;
     const int64_t limit = workspace_bytes_for(k, nvis);
     for (full.chunk = kMinAutoChunk; full.chunk < k->chunk; full.chunk *= 2)
       if (full.chunk >= want && carve(k, full, nvis, nullptr, W, !short_items) <= limit) break;
   }
   carve(k, full, nvis, base, W, !short_items);
-  if (what == Binning::kPlan) return full;
-  BinShape B = bin_shape(k, nvis, what == Binning::kDegrid);
   B.chunk = full.chunk;
   return B;
 }

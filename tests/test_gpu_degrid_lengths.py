@@ -1,5 +1,5 @@
 """Single degridding calls with supports above 8, on both sides of the rules for short work items
-(rows per tile) and for bins that keep the planes (rows, table size, copies a CU holds), untuned and tuned,
+(rows per tile) and for bins that keep the planes (counters a bin, copies a CU holds), untuned and tuned,
 with exactly the workspace that the library asks for, against the FP64 oracle."""
 
 import numpy as np
@@ -35,11 +35,12 @@ def _check(params, nvis, tuned=False):
     if tuned:
         vis = torch.ones(nvis, dtype=CDT[prec], device="cuda")
         W.autotune(k, u, vis, torch.ones(nvis, dtype=RDT[prec], device="cuda"), workspace=ws)
-    M = rng.standard_normal((1, n, n)) + 1j * rng.standard_normal((1, n, n))
+    M = rng.standard_normal((plan.n_grids, n, n)) + 1j * rng.standard_normal((plan.n_grids, n, n))
     model = torch.as_tensor(M).to(CDT[prec])
-    ref = cref.degrid(plan, tabs, uvw, model.to(torch.complex128).numpy(), nthreads=8)
+    off = None if plan.n_images == 1 else np.sort(rng.integers(11, nvis - 11, plan.n_images + 1))
+    ref = cref.degrid(plan, tabs, uvw, model.to(torch.complex128).numpy(), off, nthreads=8)
     out = torch.full((nvis,), 7.0, dtype=CDT[prec], device="cuda")
-    W.degrid(k, u, model.cuda(), out, workspace=ws)
+    W.degrid(k, u, model.cuda(), out, image_offsets=None if off is None else torch.as_tensor(off).cuda(), workspace=ws)
     got = out.to(torch.complex128).cpu().numpy()
     assert np.all(got[ref == 0] == 0)
     assert rel_max(got, ref) < TOL[prec]
@@ -55,14 +56,22 @@ def test_short_items(prec, S, nvis, tile):
                 precision=prec, n_images=1, algorithm="tiled", tile=tile), nvis)
 
 
-# 2^19 rows; 5 MB of taps (FP32 S = 12: 73.7 kB a plane); one copy a CU (FP64 tiles of 64)
+# the planes are kept with 1, 2, .. 256 counters a bin (36 tiles of 16: 16 rows a counter and at most
+# 65536), from 2^19 rows or 128 a tile on; one copy a CU (FP64 tiles of 64)
 @pytest.mark.parametrize("nvis,planes,prec,S,tile", [
-    (524287, 68, "f32", 12, 16), (524288, 68, "f32", 12, 16), (524288, 67, "f32", 12, 16), (524288, 68, "f64", 12, 16),
+    (524287, 68, "f32", 12, 16), (524288, 68, "f32", 12, 16), (524288, 2, "f32", 9, 16), (600000, 7, "f32", 10, 32),
+    (524288, 1, "f32", 9, 16), (4608, 4, "f64", 12, 16), (4608, 5, "f64", 12, 16), (30000, 2, "f64", 9, 32),
     (524287, 20, "f64", 9, 64), (524288, 20, "f64", 9, 64), (524288, 20, "f32", 9, 64),
 ])
 def test_planes_kept(nvis, planes, prec, S, tile):
     _check(dict(n=96, cell_rad=0.02 / 96, n_wplanes=planes, w_max=80.0, support=S, oversample=8, kernel_image_size=32,
                 precision=prec, n_images=1, algorithm="tiled", tile=tile), nvis)
+
+
+@pytest.mark.parametrize("images,w_mode,layers", [(3, "linear", 1), (1, "fold", 1), (1, "fold_sqrt", 1), (1, "stack", 3)])
+def test_planes_kept_modes(images, w_mode, layers):
+    _check(dict(n=96, cell_rad=0.02 / 96, n_wplanes=6, w_max=80.0, support=13, oversample=8, kernel_image_size=32,
+                precision="f64", n_images=images, algorithm="tiled", tile=16, w_mode=w_mode, n_wlayers=layers), 60000)
 
 
 @pytest.mark.parametrize("prec,S", [("f32", 9), ("f64", 13)])
