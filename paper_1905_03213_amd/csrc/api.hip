@@ -272,21 +272,25 @@ constexpr int64_t kBestCounters = 1ll << 16, kBestCountersManyRows = 1ll << 15, 
 // 1.7e5 counters (1024^2, 23 planes) 0.52 -> 0.46 ms, but 5.2e5 (2048^2, 128 planes)
 // 1.28 -> 1.37 ms.
 constexpr int64_t kMaxSpread = 1ll << 18;
-// The planes' bins skew the rows of spread counters, since tiles above each other, whose bins are
-// busy at the same time, otherwise lie in a few columns where a row of tiles has many bins in
-// common with 256.  Degridding call of 4.0e6 rows, supports 4 to 9, counters in a row, spread, and
+// The planes' bins skew the rows of spread counters where the planes divide by 4, since a plane's
+// bins in tiles near each other, which are busy at the same time, otherwise meet again every 256 /
+// gcd(planes, 256) tiles.  Degridding call of 4.0e6 rows, supports 4 to 9, counters in a row, spread, and
 // skewed: 1024^2, 32 planes 420, 567 and 415 us (aggregated 380, 523 and 377), rows channel by
 // channel 515, 762 and 478; 1200^2, 32 planes 357, 516 and 371; 512^2, 32 planes, 2.0e6 rows 270,
 // 378 and 281; a compact array's rows, 1024^2, 32 planes 1005, 805 and 861; 60 planes 393, 414 and
 // 406.  Several counters of one bin are next to each other instead and gain without (1024^2: 343,
-// 262 and 296), and so do, mostly, fewer than 4096 (2048, 256^2: 710, 730 and 866).
+// 262 and 296), and so do, mostly, fewer than 4096 (2048, 256^2: 710, 730 and 866).  Other numbers
+// of planes are spread well enough without, and a skew brings other bins together (skewed over
+// spread, degridding with supports 3 to 8 on 480^2 to 3000^2, 1.0e6 to 6.0e6 rows, 2 to 40 channels:
+// 4 planes 0.68 to 1.03, 8 0.65 to 1.01, 32 0.78 to 1.04, 64 0.79 to 1.01, 9 0.97 to 1.27, 13 0.96 to
+// 1.15, 17 0.89 to 1.08, 34 0.95 to 1.02).
 constexpr uint32_t kSkew = 101;
 constexpr int64_t kMinSkewed = 1 << 12;
 
 void set_counters(BinShape &B) {
   B.n_counts = B.n_keys << B.log2_rep;
   B.spread = B.n_counts <= kMaxSpread;
-  B.skew = B.spread && B.log2_rep == 0 && B.n_counts >= kMinSkewed ? kSkew : 0u;
+  B.skew = B.spread && B.log2_rep == 0 && B.kw % 4 == 0 && B.n_counts >= kMinSkewed ? kSkew : 0u;
 }
 
 // once_rows: rows of a single call, -1 for a kept or stable binning.
