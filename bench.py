@@ -44,7 +44,7 @@ TAP_BYTES_PER_VIS = S * S * 8    # complex FP32 taps returned to registers by 16
 # WRITE_SIZE x1.000, scale factors from a 512 MiB copy), measured at tile 32 / 8192
 # records per work item on this workload; profiles/tiled_grid_kernel_2048_S8_cfg2.md
 # has the commands and raw values.  Reported only when the run uses that configuration.
-MEASURED_TRAFFIC = {"tile": 32, "chunk": 8192, "bytes": 892.6e6}
+MEASURED_TRAFFIC = {"tile": 32, "chunk": 8192, "bytes": 1022.9e6}
 
 
 def log(*a):
