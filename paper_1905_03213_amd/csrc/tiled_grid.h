@@ -28,10 +28,10 @@
 // load (one record per half wavefront, then a half-wavefront swap), and a group's loads stay
 // one group of 16 records ahead of their use.
 //
-// What bounds it (5.6e7 records, 2048^2 grid, S = 8, 128 planes, 32-cell tiles): the path
-// from L2 to the L1 caches.  A record's 512 bytes of taps come almost always from L2 (a bin
-// of tile and plane holds fewer records than the plane has sub-kernels), 27 GB a launch at
-// 20 TB/s.  1.53 ms with readlane broadcasts, 1.73 with DPP but loads left to the compiler's
+// What bounds it (5.6e7 records, 2048^2 grid, S = 8, 128 planes, 32-cell tiles): the taps' path
+// from L2 through the L1 caches, whose data return is busy for 95 % of the launch and waits for
+// L2 in 32 % of it.  A record's 512 bytes of taps come almost always from L2 (a tile holds
+// fewer records of a plane than the plane has sub-kernels), 27 GB a launch at 20 TB/s.  1.53 ms with readlane broadcasts, 1.73 with DPP but loads left to the compiler's
 // order, 1.40 with the loads held a group ahead and 16 records a group; with 16-cell tiles
 // 1.33, and 1.05 if every tap hit L1.  Two half-wavefront gridders with a tile copy each
 // (no swap, 25 instead of 32 clocks of issue a record) took 1.54 and 1.39 ms: LDS then holds
