@@ -87,7 +87,7 @@ def hazards(listing):
     return bad, n_dpp
 
 
-def test_checker_sees_hazards():
+def test_scan_sees_hazards():
     write = "v_mov_b32_e32 v3, v7\n"
     read = "v_fmac_f64_dpp v[0:1], v[2:3], v[8:9] row_newbcast:1 row_mask:0xf bank_mask:0xf// 00FF\n"
     swap = "v_permlane16_swap_b32_e32 v50, v3\n"
