@@ -74,6 +74,12 @@ def test_planes_kept_modes(images, w_mode, layers):
                 precision="f64", n_images=images, algorithm="tiled", tile=16, w_mode=w_mode, n_wlayers=layers), 60000)
 
 
+@pytest.mark.parametrize("prec,S,nvis,planes", [("f64", 9, 60000, 3), ("f32", 12, 524288, 9), ("f32", 17, 524288, 2)])
+def test_planes_kept_aggregated(prec, S, nvis, planes):
+    _check(dict(n=96, cell_rad=0.02 / 96, n_wplanes=planes, w_max=80.0, support=S, oversample=8, kernel_image_size=32,
+                precision=prec, n_images=1, algorithm="tiled", tile=16, bin_aggregate=1), nvis)
+
+
 @pytest.mark.parametrize("prec,S", [("f32", 9), ("f64", 13)])
 def test_tuned(prec, S):
     _check(dict(n=128, cell_rad=0.02 / 128, n_wplanes=5, w_max=80.0, support=S, oversample=8, kernel_image_size=32,
